@@ -7,6 +7,7 @@
 //   K_a  alpha, zeta_j', alpha_j        (one block per RHS)
 //   K_B  r^{k+1} = r^k - alpha (Q t + s0 p0)   (stencil; partial |r|^2), into a ring slot
 //   K_b  beta, beta_j, freezing, and the block coefficients of every shift
+//        (K_a and K_b: scalars.h)
 //   K_C  p0 = r^{k+1} + beta p0
 // The ring keeps the last m residuals.  Because the shift recurrences are
 // linear, after m iterations (or when the RHS finishes) one pass applies
@@ -30,76 +31,6 @@ __global__ void k_blk_reset(Blk *bk, const MState *st, int nrhs, int nshift)
         for (int i = 0; i <= MB; i++) bk->C[r][j][i] = bk->X[r][j][i] = 0.0;
         bk->inblk[r][j] = (j < nshift) ? st->act[r][j] : 0;
         if (j == 0) bk->t[r] = 0;
-    }
-}
-
-// beta, beta_j, freezing, and the block coefficients; RHS blockIdx.x, shift
-// j in thread j.  sw2 > 0: an RHS with |r|^2 <= sw2 |b|^2 pauses (hand-over).
-__global__ __launch_bounds__(kBlock) void k_blk_beta(MState *st, Blk *bk, const double *partials, int nblk,
-                                                     int cnt, double sw2)
-{
-    __shared__ double lds[4];
-    const int r = blockIdx.x;
-    const int j = threadIdx.x;
-    if (st->skip[r]) return;
-    double a = 0.0;
-    for (int k = threadIdx.x; k < cnt; k += kBlock) a += partials[(size_t)r * nblk + k];
-    const double rr_new = block_sum_all(a, lds);
-    const int it = st->iter[r] + 1;
-    if (!isfinite(rr_new)) {
-        if (j == 0) {
-            st->iter[r] = it;
-            st->nonfinite[r] = 1;
-            st->skip[r] = 1;
-        }
-        return;
-    }
-    const double beta = rr_new / st->rr[r];
-    const double thr = st->tol2r[r] * st->bb[r];
-    const int t = bk->t[r];
-    int live = 0;
-    if (j < st->nshift && st->act_cur[r][j]) {
-        const double z = st->zeta[r][j], zn = st->zeta_new[r][j];
-        const double q = zn / z;
-        const double bj = beta * q * q;
-        const double aj = st->aj[r][j];
-        // x += a p^{(t)};  p^{(t+1)} = zn r^{(t+1)} + bj p^{(t)}
-        const double P = bk->P[r][j];
-        bk->XP[r][j] += aj * P;
-        bk->P[r][j] = bj * P;
-        for (int i = 1; i <= t; i++) {
-            const double c = bk->C[r][j][i];
-            bk->X[r][j][i] += aj * c;
-            bk->C[r][j][i] = bj * c;
-        }
-        bk->C[r][j][t + 1] = zn;
-        st->bj[r][j] = bj;
-        st->zeta_old[r][j] = z;
-        st->zeta[r][j] = zn;
-        if (zn * zn * rr_new <= thr) {
-            st->act[r][j] = 0;
-            st->frozen_at[r][j] = it;
-            st->frozen_rr[r][j] = zn * zn * rr_new;
-        } else {
-            live = 1;
-        }
-    }
-    // also the barrier between every thread's reads of rr, iter and t and
-    // thread 0's writes below
-    const int left = __syncthreads_count(live);
-    if (j == 0) {
-        st->iter[r] = it;
-        st->beta[r] = beta;
-        bk->t[r] = t + 1;
-        st->rr[r] = rr_new;
-        st->alpha_old[r] = st->alpha[r];
-        st->run_c[r] = left ? 1 : 0;
-        if (!left) {
-            st->skip[r] = 1;
-        } else if (sw2 > 0.0 && rr_new <= sw2 * st->bb[r]) {
-            st->paused[r] = 1;
-            st->skip[r] = 1;
-        }
     }
 }
 
@@ -230,19 +161,27 @@ struct El<P_F32> {
     }
 };
 
-// p0 = r_new + beta p0 on RHS that are still iterating or paused in this
-// iteration (run_c).  Non-temporal loads: FP64 214 -> 194 us, FP32 89 -> 86 us
+// p0 = r_new + beta p0 on the RHS of this iteration (run_c; also one that it
+// finishes, whose p0 nothing reads, or pauses).  With the beta stage aboard
+// (pro.kind) the first block of each RHS runs it and the others form beta
+// themselves.  Non-temporal loads: FP64 214 -> 194 us, FP32 89 -> 86 us
 // at 32^3x64 (a non-temporal store as well made it slower).
 template <int PS>
-__global__ __launch_bounds__(kBlock) void k_base_p(Geom g, int nb, const MState *st, const void *rnv, void *p0v)
+__global__ __launch_bounds__(kBlock) void k_base_p(Geom g, int nb, const MState *st, const void *rnv, void *p0v,
+                                                   ProArgs pro)
 {
     using E = El<PS>;
+    __shared__ double lds[4];
     const int r = blockIdx.y;
+    const int b = (int)blockIdx.x - (pro.kind ? 1 : 0);
+    if (b < 0) {
+        beta_stage<kBlock>(pro, r, lds);
+        return;
+    }
     if (!st->run_c[r]) return;
-    const int b = blockIdx.x;
+    const double be = pro.kind ? pro_beta<kBlock>(pro, r, lds) : st->beta[r];
     const int p = b / nb, i = (b % nb) * kBlock + threadIdx.x;
     if (i >= g.Vh) return;
-    const double be = st->beta[r];
 #pragma unroll
     for (int e = 0; e < E::N; e++) {
         double ar[E::C], ai[E::C], qr[E::C], qi[E::C];
@@ -532,7 +471,7 @@ size_t blocked_ws_bytes(const Lat &L, int nrhs, int nshift, int m, bool keep_x, 
     const size_t F = field_bytes(P_F64, L.V), FS = field_bytes(ps, L.V);
     c.take(sizeof(MState));
     c.take(sizeof(Blk));
-    c.take(sizeof(double) * 2 * nrhs * site_blocks(L));
+    c.take(sizeof(double) * 3 * nrhs * part_stride(L));
     c.take(sizeof(double) * 4 * NR);
     if (ps == P_F48) {
         // p_j first, then the ring, p0 and t, spanning at least nrhs*nshift
@@ -567,6 +506,7 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
     const int R = b.nrhs;
     const int nblk = site_blocks(L);
     const int npart = stencil_partials(L, PS, R);   // slots the iteration stencils fill
+    const int pstr = part_stride(L);
     const int m = o.m;
     if (m < 1 || m > MB || R > NR) return OVL_ERR_INVALID;
     if (o.reliable && !o.keep_x) return OVL_ERR_INVALID;
@@ -580,7 +520,10 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
     const size_t F = field_bytes(P_F64, L.V), FS = field_bytes(PS, L.V);
     MState *S = (MState *)c.take(sizeof(MState));
     Blk *BK = (Blk *)c.take(sizeof(Blk));
-    double *partials = (double *)c.take(sizeof(double) * 2 * R * nblk);
+    // the first stencil's sums (two per RHS), then the second's: a launch that
+    // carries a scalar stage reads the other's while it writes its own
+    double *partials = (double *)c.take(sizeof(double) * 3 * R * pstr);
+    double *partials2 = partials + (size_t)2 * R * pstr;
     double *red = (double *)c.take(sizeof(double) * 4 * NR);
     char *ring;
     Fld p0{nullptr, nullptr, PS, R}, t{nullptr, nullptr, PS, R}, pj{nullptr, nullptr, PS, R * nshift};
@@ -676,16 +619,27 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
     B.p = p0.d;
     B.shiftv = S->s0r;
     B.alpha = S->alpha;
+    B.partials = partials2;
 
     Prof prof;
     prof.on = prm->profile != 0 && stats;
     prof.stencil_only = prm->profile == 2;
     prof.st = st;
+    // The scalar stages ride in the launches that follow them: alpha in the
+    // second stencil, beta in the next iteration's first one (W_SNORM) or in
+    // the p0 update, in kernels of their own only at a block's end, in a
+    // streaming launch (carries_scalars) or when each scalar kernel is to be
+    // timed.  At 16^3x32 that takes two launches and 11 us of scalar kernels
+    // out of an iteration of 72 us (48-bit) or 42 us (FP32).
+    const double sw2 = o.switch_rel * o.switch_rel;
+    const bool carry = carries_scalars(L, PS, R) && !o.f16.d && !(prof.on && !prof.stencil_only);
+    const ProArgs none{};
+    const ProArgs pa{PRO_ALPHA, npart, pstr, partials, S, nullptr, 0.0};
+    const ProArgs pb{PRO_BETA, npart, pstr, partials2, S, BK, sw2};
     long k = 0;
     int passes = 0, replacements = 0;
     bool done = false, switched = false;
     const double rd2 = prm->reliable_delta * prm->reliable_delta;
-    const double sw2 = o.switch_rel * o.switch_rel;
     long it_left = prm->maxiter;
     for (int q = 0; q < R; q++) it_left = std::min<long>(it_left, prm->maxiter - it0[q]);
     // the next block's length (below); |r|^2 at the last block end
@@ -716,7 +670,8 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
                 At.in = slot(k);
                 At.p = t.d;
                 At.shiftv = S->beta;
-                OVL_HIP(launch_wilson(L, PS, W_SNORM, true, At, st, v0, v1));
+                // (at a block's start beta is in the state)
+                OVL_HIP(launch_wilson(L, PS, W_SNORM, true, At, st, v0, v1, carry && q > 0 ? &pb : nullptr));
             } else if (trec) {
                 // t = Q p0 directly: p0 = r0 at the start of a fresh solve, the
                 // handed-over p0 at the start of a resumed one, p_j0 at a block start
@@ -728,19 +683,23 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
                 OVL_HIP(launch_wilson(L, PS, W_NORM, true, A, st, v0, v1));
             }
             if (f16) OVL_HIP(round16(t.d));
-            prof.pair(OVL_K_SCALAR, &v0, &v1);
-            launch_k(k_ms_alpha, dim3(R), dim3(kBlock), st, v0, v1, S, (const double *)partials, nblk, npart);
+            if (!carry) {
+                prof.pair(OVL_K_SCALAR, &v0, &v1);
+                launch_k(k_ms_alpha, dim3(R), dim3(kBlock), st, v0, v1, pa);
+            }
             B.rin = slot(k);
             B.out = slot(k + 1);
             prof.pair(OVL_K_STENCIL, &v0, &v1);
-            OVL_HIP(launch_wilson(L, PS, rmode, true, B, st, v0, v1));
+            OVL_HIP(launch_wilson(L, PS, rmode, true, B, st, v0, v1, carry ? &pa : nullptr));
             if (f16) OVL_HIP(round16(slot(k + 1)));
-            prof.pair(OVL_K_SCALAR, &v0, &v1);
-            launch_k(k_blk_beta, dim3(R), dim3(kBlock), st, v0, v1, S, BK, (const double *)partials, nblk, npart, sw2);
+            if (!carry || (trec && q + 1 == batch)) {
+                prof.pair(OVL_K_SCALAR, &v0, &v1);
+                launch_k(k_ms_beta, dim3(R), dim3(kBlock), st, v0, v1, pb);
+            }
             if (!trec) {
                 prof.pair(OVL_K_UPDATE, &v0, &v1);
-                launch_k(k_base_p<PS>, sgrid, dim3(kBlock), st, v0, v1, L.g, L.nb, (const MState *)S,
-                         (const void *)slot(k + 1), p0.d);
+                launch_k(k_base_p<PS>, dim3(nblk + (carry ? 1 : 0), R), dim3(kBlock), st, v0, v1, L.g, L.nb,
+                         (const MState *)S, (const void *)slot(k + 1), p0.d, carry ? pb : none);
             }
             if (f16) OVL_HIP(round16(p0.d));
             OVL_HIP(hipGetLastError());
@@ -832,7 +791,7 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
             Q2.alpha = S->one;
             Q2.partials = partials;
             OVL_HIP(launch_wilson(L, P_F64, rmode, true, Q2, st));
-            OVL_HIP(launch_reduce(partials, 1, R, nblk, red, st));
+            OVL_HIP(launch_reduce(partials, 1, R, pstr, red, st, stencil_partials(L, P_F64, R)));
             Fld cur{slot(k), nullptr, PS, R};
             OVL_HIP(launch_convert(L, s2, cur, st));
             k_set_rr<<<1, 64, 0, st>>>(S, red, R);

@@ -88,6 +88,15 @@ struct Geom {
     int Mfma;      // FP32 D_W on several RHS by the matrix-core stencil
 };
 
+// A tile of the stencil's tile form (wilson_tile.h): its extents, the tiles per
+// direction and the multipliers that divide by the extents (n / d = n * m >> 20,
+// exact for n < 512 and d <= 512).  nt threads a block; nt = 0: no tiles.
+struct Tile {
+    int T[4], N[4];
+    unsigned m3, m2, m1;
+    int nt;
+};
+
 // Threads (sites) per block of the time-streaming stencil with ts slices per
 // thread: 256, or 192 when whole x3 rows tile 192 sites but not 256 (x3
 // extents such as 24 and 48), so that the LDS-staged build applies.  192 only
@@ -574,14 +583,18 @@ __device__ __forceinline__ double block_sum_w(double v, double *lds /* >= 4 */)
     if constexpr (NW == 4) {
         return block_sum(v, lds);
     } else {
-        static_assert(NW == 3, "block_sum_w: 3 or 4 waves");
+        static_assert(NW == 3 || NW == 8, "block_sum_w: 3, 4 or 8 waves");
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
         int w = threadIdx.x >> 6;
         if ((threadIdx.x & 63) == 0) lds[w] = v;
         __syncthreads();
         double t = 0.0;
-        if (threadIdx.x == 0) t = (lds[0] + lds[1]) + lds[2];
+        if (threadIdx.x == 0) {
+            t = lds[0] + lds[1];
+            if constexpr (NW == 3) t += lds[2];
+            if constexpr (NW == 8) t = (t + (lds[2] + lds[3])) + ((lds[4] + lds[5]) + (lds[6] + lds[7]));
+        }
         __syncthreads();
         return t;
     }

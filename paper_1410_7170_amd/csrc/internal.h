@@ -15,6 +15,7 @@ struct Lat {
     int64_t V;
     int Vh;
     int nb;        // blocks per parity of a site-parallel launch
+    Tile tile;     // of the stencil's tile form
 };
 
 Lat make_lat(const ovl_lattice *lat);
@@ -63,9 +64,14 @@ inline Fld sub(const Fld &f, int64_t V, int first, int count)
 }
 
 // ---- launchers (return hipError_t of the launch)
-// e0, e1 (optional): events the launch records at the stencil's start and end
+// e0, e1 (optional): events the launch records at the stencil's start and end;
+// pro (optional): a scalar stage it carries
 hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hipStream_t st, hipEvent_t e0 = nullptr,
-                         hipEvent_t e1 = nullptr);
+                         hipEvent_t e1 = nullptr, const ProArgs *pro = nullptr);
+
+// the tile form's kernel (wilson_tile.hip), for launch_wilson
+hipError_t launch_wilson_tile(int prec, int mode, bool g5, dim3 grid, const WArgs &a, const Tile &t,
+                              const ProArgs &pro, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
 
 // A kernel launch that, given events, has its own dispatch record them at the
 // kernel's start and end (no marker packets in the queue); args must have the
@@ -86,7 +92,9 @@ hipError_t launch_norm2(const Lat &L, Fld f, double *partials, hipStream_t st);
 hipError_t launch_diff_norm2(const Lat &L, Fld a, Fld b, double *partials, hipStream_t st);
 hipError_t launch_dot(const Lat &L, Fld a, Fld b, double *partials, hipStream_t st);
 // out[q*nrhs + r] = sum of partials[(q*nrhs + r)*nblk ...]
-hipError_t launch_reduce(const double *partials, int nq, int nrhs, int nblk, double *out, hipStream_t st);
+// (nblk: row stride, of which the first cnt slots count; cnt < 0: all)
+hipError_t launch_reduce(const double *partials, int nq, int nrhs, int nblk, double *out, hipStream_t st,
+                         int cnt = -1);
 // y = a*x + b*y (FP64 or FP32 fields; per-RHS coefficients on device or host)
 hipError_t launch_convert(const Lat &L, Fld src, Fld dst, hipStream_t st);
 hipError_t launch_axpby(const Lat &L, double a, Fld x, double b, Fld y, hipStream_t st);
@@ -106,14 +114,22 @@ int site_blocks(const Lat &L);           // blocks of a flat elementwise launch 
 // lanes per site (RHS tile) and nt >> kr sites per block; ts = 0: one thread
 // per site and RHS.  blocks_per_tile: blocks of one RHS tile (each fills one
 // partial-sum slot per RHS of the tile).
+// ts = 0 and tile.nt > 0: the tile form.
 struct StencilShape {
     int ts, nt, kr, blocks_per_tile, ntile;
+    Tile tile;
 };
 StencilShape stencil_shape(const Lat &L, int prec, int nrhs);
-// Leading per-RHS partial-sum slots a stencil launch of this precision on
-// nrhs fields fills; it zeroes the rest of the site_blocks(L) slots, so a
-// consumer may sum only these (the same sum bit for bit).
+Tile pick_tile(const int E[4], int64_t V);
+// Partial-sum slots that a stencil launch of this precision on nrhs fields
+// fills, and the row stride (slots allocated) of its partials.
 int stencil_partials(const Lat &L, int prec, int nrhs);
+int part_stride(const Lat &L);
+// Whether such a launch may carry a scalar stage of the multishift CG
+// (scalars.h): the one-site and tile forms on small lattices, whose short blocks
+// hide it; a streaming launch has exactly the blocks that are resident at once,
+// and one more would run after them.
+bool carries_scalars(const Lat &L, int prec, int nrhs);
 
 // Even-odd reduced Wilson solve (wilson_eo.hip): D_W(m0) x = b per RHS, to
 // |b - D_W x| <= tol |b| (true_res) or maxiter CGLS iterations (iters).

@@ -25,6 +25,7 @@ Lat make_lat(const ovl_lattice *lat)
     L.g.Kr = lat->rhs_tile >= 8 ? 3 : lat->rhs_tile >= 4 ? 2 : lat->rhs_tile >= 2 ? 1 : 0;
     L.g.Mfma = lat->mfma;
     L.nb = (L.Vh + kBlock - 1) / kBlock;
+    L.tile = pick_tile(L.g.L, L.V);
     return L;
 }
 
@@ -37,15 +38,6 @@ int hip_fail(hipError_t e)
 int last_hip_error() { return g_last_hip; }
 
 int site_blocks(const Lat &L) { return 2 * L.nb; }
-
-// The time-streaming stencil (FP64, FP32 with a stream length) runs
-// blocks_per_tile blocks per RHS tile, one partial slot each; the one-site
-// form fills all 2 nb slots.
-int stencil_partials(const Lat &L, int prec, int nrhs)
-{
-    const StencilShape sh = stencil_shape(L, prec, nrhs);
-    return sh.ts > 0 ? sh.blocks_per_tile : 2 * L.nb;
-}
 
 // ---------------------------------------------------------------- pack
 template <int PREC>
@@ -237,12 +229,12 @@ __global__ __launch_bounds__(kBlock) void k_dot_f64(Geom g, int nb, int nrhs, co
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_reduce(const double *partials, int nblk, double *out)
+__global__ __launch_bounds__(kBlock) void k_reduce(const double *partials, int nblk, int cnt, double *out)
 {
     __shared__ double lds[4];
     const double *src = partials + (size_t)blockIdx.x * nblk;
     double v = 0.0;
-    for (int k = threadIdx.x; k < nblk; k += kBlock) v += src[k];
+    for (int k = threadIdx.x; k < cnt; k += kBlock) v += src[k];
     double t = block_sum(v, lds);
     if (threadIdx.x == 0) out[blockIdx.x] = t;
 }
@@ -338,9 +330,9 @@ hipError_t launch_dot(const Lat &L, Fld a, Fld b, double *partials, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const double *partials, int nq, int nrhs, int nblk, double *out, hipStream_t st)
+hipError_t launch_reduce(const double *partials, int nq, int nrhs, int nblk, double *out, hipStream_t st, int cnt)
 {
-    k_reduce<<<nq * nrhs, kBlock, 0, st>>>(partials, nblk, out);
+    k_reduce<<<nq * nrhs, kBlock, 0, st>>>(partials, nblk, cnt < 0 ? nblk : cnt, out);
     return hipGetLastError();
 }
 

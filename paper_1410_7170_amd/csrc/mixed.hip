@@ -92,7 +92,7 @@ size_t mixed_ws_bytes(const Lat &L, int nrhs, int nshift_caller, int m, int m64,
     c.take(F * nrhs);                                 // residual scratch
     c.take(F * nrhs);
     c.take(F * nrhs);                                 // base residual at the hand-over
-    c.take(sizeof(double) * 2 * NR * site_blocks(L));
+    c.take(sizeof(double) * 2 * NR * part_stride(L));
     c.take(sizeof(double) * 4 * NR);
     c.take(sizeof(double) * NR * NS);                 // shift of each (shift, RHS) field
     c.take(sizeof(double) * NR * NS);                 // zeta at the hand-over of each field
@@ -160,7 +160,7 @@ static int mixed_solve(const Lat &L, const ovl_gauge *U, double m0, int nshift, 
     Fld T{c.take(F * R), nullptr, P_F64, R};
     Fld Res{c.take(F * R), nullptr, P_F64, R};
     Fld R0{c.take(F * R), nullptr, P_F64, R};
-    double *partials = (double *)c.take(sizeof(double) * 2 * NR * site_blocks(L));
+    double *partials = (double *)c.take(sizeof(double) * 2 * NR * part_stride(L));
     double *red = (double *)c.take(sizeof(double) * 4 * NR);
     double *fsh = (double *)c.take(sizeof(double) * NR * NS);
     double *fze = (double *)c.take(sizeof(double) * NR * NS);
@@ -293,7 +293,7 @@ static int mixed_solve(const Lat &L, const ovl_gauge *U, double m0, int nshift, 
             B.rin_scale = fze + c0;
             B.partials = partials;
             OVL_HIP(launch_wilson(L, P_F64, W_RESNORM, true, B, st));
-            OVL_HIP(launch_reduce(partials, 1, nc, nblk, red, st));
+            OVL_HIP(launch_reduce(partials, 1, nc, part_stride(L), red, st, stencil_partials(L, P_F64, nc)));
             double h[NR];
             OVL_HIP(hipMemcpyAsync(h, red, sizeof(double) * nc, hipMemcpyDeviceToHost, st));
             OVL_HIP(hipStreamSynchronize(st));

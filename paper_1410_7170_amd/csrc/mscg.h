@@ -8,10 +8,6 @@
 
 namespace ovl {
 
-constexpr int NR = OVL_MAX_RHS;
-constexpr int NS = OVL_MAX_SHIFTS;
-constexpr int MB = OVL_MAX_BLOCK;   // longest block of the blocked shift update
-
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 // Block lengths of the mixed solver's phases: FP32 phase (block, default 32)
@@ -31,44 +27,6 @@ struct WsCarve {
         off += align256(n);
         return p;
     }
-};
-
-// Coefficients of the blocked shift update.  Over a block of iterations
-// k0..k0+T-1 the shift recurrences x_j += a_j p_j, p_j = z_j' r + b_j p_j are
-// linear in the block-start p_j and the stored residuals r^{k0+1..k0+T}:
-//   p_j^{k0+t} = P p_j^{k0} + sum_{i<=t} C_i r^{k0+i},
-//   x_j^{k0+T} = x_j^{k0} + XP p_j^{k0} + sum_i X_i r^{k0+i}.
-struct Blk {
-    double P[NR][NS], XP[NR][NS];
-    double C[NR][NS][MB + 1], X[NR][NS][MB + 1];
-    int inblk[NR][NS];   // shift active when the block started
-    int t[NR];           // iterations done in the current block
-};
-// Scalar state of a multishift CG on (Q^2 + s_j) x_j = b, one system per RHS,
-// kept in device memory so the iteration runs without host round trips.
-struct MState {
-    double rr[NR], bb[NR], alpha[NR], alpha_old[NR], beta[NR];
-    double zeta[NR][NS], zeta_old[NR][NS], zeta_new[NR][NS], aj[NR][NS], bj[NR][NS];
-    double delta[NS];      // s_j - s0 (shift offsets from the base shift)
-    double s0r[NR];        // base shift of each RHS system
-    double tol2r[NR];      // squared relative tolerance of each RHS system
-    int act[NR][NS];       // shift still iterating
-    int act_cur[NR][NS];   // shifts updated in the current iteration
-    int frozen_at[NR][NS];
-    double frozen_rr[NR][NS];   // zeta^2 |r|^2 of a shift at the iteration it froze
-    int iter[NR];
-    int skip[NR];          // RHS finished (every shift frozen) or failed
-    int nonfinite[NR];
-    int nrhs, nshift;
-    // reliable-update bookkeeping (mixed solver)
-    double rr_ref[NR];     // |r|^2 at the last residual replacement
-    int want_update[NR];
-    // hand-over to another precision: an RHS whose base residual reached the
-    // hand-over level stops (skip set, paused set) until the solve that
-    // continues its recurrences clears both
-    int paused[NR];
-    int run_c[NR];         // the iteration's p0 update is due (set by K_b, cleared by K_a)
-    double one[NR];        // 1 per RHS: the alpha of a residual replacement's update stencil
 };
 
 struct ShiftWeights {
@@ -121,8 +79,10 @@ struct MsScratch {
     void *xlend = nullptr;
 };
 
-// alpha and the shifted zeta_j', alpha_j (one block per RHS); defined in solver.hip
-__global__ void k_ms_alpha(MState *st, const double *partials, int nblk, int cnt);
+// The scalar stages in kernels of their own, one block per RHS (scalars.h);
+// defined in solver.hip
+__global__ void k_ms_alpha(ProArgs a);
+__global__ void k_ms_beta(ProArgs a);
 
 // Upload the constant part of the scalar state (per-RHS base shift and
 // tolerance default to the smallest shift and prm->tol), |b|^2 per RHS and

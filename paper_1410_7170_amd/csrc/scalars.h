@@ -1,0 +1,240 @@
+// Device-resident scalar state of the multishift CG and the two scalar stages
+// of an iteration: alpha after the first stencil's norms, beta after the
+// second's.  A stage runs either in a kernel of its own (one block per RHS) or
+// inside a stencil launch: then every block of the launch forms the one value
+// its sites need (alpha or beta) from the previous launch's partial sums, and
+// one extra block per RHS runs the whole stage beside them.
+#pragma once
+
+#include "../../include/ovl.h"
+#include "device.h"
+
+namespace ovl {
+
+constexpr int NR = OVL_MAX_RHS;
+constexpr int NS = OVL_MAX_SHIFTS;
+constexpr int MB = OVL_MAX_BLOCK;   // longest block of the blocked shift update
+
+// Coefficients of the blocked shift update.  Over a block of iterations
+// k0..k0+T-1 the shift recurrences x_j += a_j p_j, p_j = z_j' r + b_j p_j are
+// linear in the block-start p_j and the stored residuals r^{k0+1..k0+T}:
+//   p_j^{k0+t} = P p_j^{k0} + sum_{i<=t} C_i r^{k0+i},
+//   x_j^{k0+T} = x_j^{k0} + XP p_j^{k0} + sum_i X_i r^{k0+i}.
+struct Blk {
+    double P[NR][NS], XP[NR][NS];
+    double C[NR][NS][MB + 1], X[NR][NS][MB + 1];
+    int inblk[NR][NS];   // shift active when the block started
+    int t[NR];           // iterations done in the current block
+};
+// Scalar state of a multishift CG on (Q^2 + s_j) x_j = b, one system per RHS,
+// kept in device memory so the iteration runs without host round trips.
+struct MState {
+    double rr[NR], bb[NR], alpha[NR], alpha_old[NR], beta[NR];
+    double zeta[NR][NS], zeta_old[NR][NS], zeta_new[NR][NS], aj[NR][NS], bj[NR][NS];
+    double delta[NS];      // s_j - s0 (shift offsets from the base shift)
+    double s0r[NR];        // base shift of each RHS system
+    double tol2r[NR];      // squared relative tolerance of each RHS system
+    int act[NR][NS];       // shift still iterating
+    int act_cur[NR][NS];   // shifts updated in the current iteration
+    int frozen_at[NR][NS];
+    double frozen_rr[NR][NS];   // zeta^2 |r|^2 of a shift at the iteration it froze
+    int iter[NR];
+    int skip[NR];          // RHS finished (every shift frozen) or failed
+    int nonfinite[NR];
+    int nrhs, nshift;
+    // reliable-update bookkeeping (mixed solver)
+    double rr_ref[NR];     // |r|^2 at the last residual replacement
+    int want_update[NR];
+    // hand-over to another precision: an RHS whose base residual reached the
+    // hand-over level stops (skip set, paused set) until the solve that
+    // continues its recurrences clears both
+    int paused[NR];
+    int run_c[NR];         // the RHS takes part in this iteration: its p0 update is due (set and cleared by K_a)
+    double one[NR];        // 1 per RHS: the alpha of a residual replacement's update stencil
+    double rr_iter[NR];    // |r|^2 at the start of this iteration (set by K_a): what beta divides by
+                           // in the blocks that run beside the beta stage, which replaces rr
+};
+
+enum { PRO_NONE = 0, PRO_ALPHA = 1, PRO_BETA = 2 };
+
+// A scalar stage carried by a kernel: its partial sums (row stride pstride, of
+// which the first pcnt slots count) and the state it updates.
+struct ProArgs {
+    int kind;
+    int pcnt, pstride;
+    const double *pin;
+    MState *st;
+    Blk *bk;       // PRO_BETA: block coefficients (null: none kept)
+    double sw2;    // PRO_BETA: pause an RHS with |r|^2 <= sw2 |b|^2 (0: never)
+};
+
+// Sum of n slots, valid in every thread of a block of NT threads.  The order
+// does not depend on NT: 256 strided sums, a butterfly over each 64 of them,
+// then those four in pairs; so a stage gives the same bits in its own kernel
+// and in any stencil that carries it.
+template <int NT>
+__device__ __forceinline__ double slot_sum(const double *p, int n, double *lds /* >= 4 */)
+{
+    static_assert(NT == 256 || NT == 512, "slot_sum: block size");
+    double v = 0.0;
+    if (threadIdx.x < 256)
+        for (int k = threadIdx.x; k < n; k += 256) v += p[k];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (threadIdx.x < 256 && (threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    const double t = (lds[0] + lds[1]) + (lds[2] + lds[3]);
+    __syncthreads();
+    return t;
+}
+
+// |t|^2 + s0 |p|^2, alpha's denominator (an unshifted base needs no |p|^2: its
+// t stencil writes only the first set of partials)
+template <int NT>
+__device__ __forceinline__ double alpha_den(const ProArgs &a, int r, double *lds)
+{
+    const double tt = slot_sum<NT>(a.pin + (size_t)r * a.pstride, a.pcnt, lds);
+    const double s0 = a.st->s0r[r];
+    if (s0 == 0.0) return tt;
+    const double pp = slot_sum<NT>(a.pin + (size_t)(a.st->nrhs + r) * a.pstride, a.pcnt, lds);
+    return fma(s0, pp, tt);
+}
+
+// alpha for RHS r in a block whose sites need it; false if it is not finite
+// (the stage's own block then ends the RHS)
+template <int NT>
+__device__ __forceinline__ bool pro_alpha(const ProArgs &a, int r, double *lds, double *alpha)
+{
+    const double pq = alpha_den<NT>(a, r, lds);
+    *alpha = a.st->rr[r] / pq;
+    return isfinite(*alpha) && pq > 0.0;
+}
+
+// beta for RHS r in a block whose sites need it
+template <int NT>
+__device__ __forceinline__ double pro_beta(const ProArgs &a, int r, double *lds)
+{
+    return slot_sum<NT>(a.pin + (size_t)r * a.pstride, a.pcnt, lds) / a.st->rr_iter[r];
+}
+
+// K_a: alpha and the shifted zeta_j', alpha_j of RHS r; shift j is thread j
+// (NS <= 64: all in wave 0)
+template <int NT>
+__device__ __forceinline__ void alpha_stage(const ProArgs &a, int r, double *lds)
+{
+    MState *st = a.st;
+    const int j = threadIdx.x;
+    if (st->skip[r]) {
+        if (j == 0) st->run_c[r] = 0;
+        if (j < NS) st->act_cur[r][j] = 0;
+        return;
+    }
+    const double pq = alpha_den<NT>(a, r, lds);
+    const double rr = st->rr[r];
+    const double alpha = rr / pq;
+    if (!isfinite(alpha) || !(pq > 0.0)) {
+        if (j < st->nshift) st->act_cur[r][j] = 0;
+        if (j == 0) {
+            st->run_c[r] = 0;
+            st->nonfinite[r] = 1;
+            st->skip[r] = 1;
+        }
+        return;
+    }
+    if (j == 0) {
+        st->run_c[r] = 1;
+        st->alpha[r] = alpha;
+        st->rr_iter[r] = rr;
+    }
+    if (j < st->nshift) {
+        const int on = st->act[r][j];
+        st->act_cur[r][j] = on;
+        if (on) {
+            const double ao = st->alpha_old[r], be = st->beta[r];
+            const double z = st->zeta[r][j], zo = st->zeta_old[r][j];
+            const double zn = z * zo * ao / (alpha * be * (zo - z) + zo * ao * (1.0 + alpha * st->delta[j]));
+            st->zeta_new[r][j] = zn;
+            st->aj[r][j] = alpha * zn / z;
+        }
+    }
+}
+
+// K_b: beta, beta_j, freezing of shifts and (bk) the block coefficients of RHS
+// r; shift j is thread j.  sw2 > 0: an RHS with |r|^2 <= sw2 |b|^2 pauses
+// (hand-over).
+template <int NT>
+__device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
+{
+    MState *st = a.st;
+    Blk *bk = a.bk;
+    const int j = threadIdx.x;
+    if (st->skip[r]) return;
+    const double rr_new = slot_sum<NT>(a.pin + (size_t)r * a.pstride, a.pcnt, lds);
+    const int it = st->iter[r] + 1;
+    if (!isfinite(rr_new)) {
+        if (j == 0) {
+            st->iter[r] = it;
+            st->nonfinite[r] = 1;
+            st->skip[r] = 1;
+        }
+        return;
+    }
+    const double beta = rr_new / st->rr_iter[r];
+    const double thr = st->tol2r[r] * st->bb[r];
+    const int t = bk ? bk->t[r] : 0;
+    int live = 0;
+    if (j < st->nshift && st->act_cur[r][j]) {
+        const double z = st->zeta[r][j], zn = st->zeta_new[r][j];
+        const double q = zn / z;
+        const double bj = beta * q * q;
+        if (bk) {
+            const double aj = st->aj[r][j];
+            // x += a p^{(t)};  p^{(t+1)} = zn r^{(t+1)} + bj p^{(t)}
+            const double P = bk->P[r][j];
+            bk->XP[r][j] += aj * P;
+            bk->P[r][j] = bj * P;
+            for (int i = 1; i <= t; i++) {
+                const double c = bk->C[r][j][i];
+                bk->X[r][j][i] += aj * c;
+                bk->C[r][j][i] = bj * c;
+            }
+            bk->C[r][j][t + 1] = zn;
+        }
+        st->bj[r][j] = bj;
+        st->zeta_old[r][j] = z;
+        st->zeta[r][j] = zn;
+        if (zn * zn * rr_new <= thr) {
+            st->act[r][j] = 0;
+            st->frozen_at[r][j] = it;
+            st->frozen_rr[r][j] = zn * zn * rr_new;
+        } else {
+            live = 1;
+        }
+    }
+    // also the barrier between every thread's reads of rr, iter and t and
+    // thread 0's writes below
+    const int left = __syncthreads_count(live);
+    if (j == 0) {
+        st->iter[r] = it;
+        st->beta[r] = beta;
+        if (bk) bk->t[r] = t + 1;
+        st->rr[r] = rr_new;
+        st->alpha_old[r] = st->alpha[r];
+        if (!left) {
+            st->skip[r] = 1;
+        } else if (a.sw2 > 0.0 && rr_new <= a.sw2 * st->bb[r]) {
+            st->paused[r] = 1;
+            st->skip[r] = 1;
+        }
+    }
+}
+
+// The stage's own block inside a launch that carries it.
+template <int NT>
+__device__ __forceinline__ void pro_stage(const ProArgs &a, int r, double *lds)
+{
+    if (a.kind == PRO_ALPHA) alpha_stage<NT>(a, r, lds);
+    else beta_stage<NT>(a, r, lds);
+}
+
+}  // namespace ovl

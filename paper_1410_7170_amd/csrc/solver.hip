@@ -43,100 +43,16 @@ __global__ void k_ms_init(MState *st, const double *bb, int nrhs, int nshift, in
     }
 }
 
-// alpha and the shifted zeta_j', alpha_j for RHS blockIdx.x; the partials
-// have row stride nblk, of which the first cnt slots can be nonzero
-__global__ __launch_bounds__(kBlock) void k_ms_alpha(MState *st, const double *partials, int nblk, int cnt)
-{
-    __shared__ double lds[8];
-    const int r = blockIdx.x;
-    const int nr = st->nrhs;
-    const int j = threadIdx.x;   // shift j is thread j (NS <= 64: all in wave 0)
-    // the previous iteration's p0 update has run (stream order)
-    if (j == 0) st->run_c[r] = 0;
-    if (st->skip[r]) {
-        if (j < NS) st->act_cur[r][j] = 0;
-        return;
-    }
-    // |t|^2 + s0 |p|^2; an unshifted base needs no |p|^2 (its t stencil writes
-    // only the first set of partials)
-    const double s0 = st->s0r[r];
-    double a = 0.0, b = 0.0;
-    for (int k = threadIdx.x; k < cnt; k += kBlock) {
-        a += partials[(size_t)r * nblk + k];
-        if (s0 != 0.0) b += partials[(size_t)(nr + r) * nblk + k];
-    }
-    const double tt = block_sum_all(a, lds);
-    const double pp = block_sum_all(b, lds + 4);
-    const double pq = tt + s0 * pp;
-    const double alpha = st->rr[r] / pq;
-    if (!isfinite(alpha) || !(pq > 0.0)) {
-        if (j < st->nshift) st->act_cur[r][j] = 0;
-        if (j == 0) {
-            st->nonfinite[r] = 1;
-            st->skip[r] = 1;
-        }
-        return;
-    }
-    if (j == 0) st->alpha[r] = alpha;
-    if (j < st->nshift) {
-        const int on = st->act[r][j];
-        st->act_cur[r][j] = on;
-        if (on) {
-            const double ao = st->alpha_old[r], be = st->beta[r];
-            const double z = st->zeta[r][j], zo = st->zeta_old[r][j];
-            const double zn = z * zo * ao / (alpha * be * (zo - z) + zo * ao * (1.0 + alpha * st->delta[j]));
-            st->zeta_new[r][j] = zn;
-            st->aj[r][j] = alpha * zn / z;
-        }
-    }
-}
-
-// beta, beta_j, freezing; RHS blockIdx.x, shift j in thread j
-__global__ __launch_bounds__(kBlock) void k_ms_beta(MState *st, const double *partials, int nblk, int cnt)
+__global__ __launch_bounds__(kBlock) void k_ms_alpha(ProArgs a)
 {
     __shared__ double lds[4];
-    const int r = blockIdx.x;
-    const int j = threadIdx.x;
-    if (st->skip[r]) return;
-    double a = 0.0;
-    for (int k = threadIdx.x; k < cnt; k += kBlock) a += partials[(size_t)r * nblk + k];
-    const double rr_new = block_sum_all(a, lds);
-    const int it = st->iter[r] + 1;
-    if (!isfinite(rr_new)) {
-        if (j == 0) {
-            st->iter[r] = it;
-            st->nonfinite[r] = 1;
-            st->skip[r] = 1;
-        }
-        return;
-    }
-    const double beta = rr_new / st->rr[r];
-    const double thr = st->tol2r[r] * st->bb[r];
-    int live = 0;
-    if (j < st->nshift && st->act_cur[r][j]) {
-        const double z = st->zeta[r][j], zn = st->zeta_new[r][j];
-        const double q = zn / z;
-        st->bj[r][j] = beta * q * q;
-        st->zeta_old[r][j] = z;
-        st->zeta[r][j] = zn;
-        if (zn * zn * rr_new <= thr) {
-            st->act[r][j] = 0;
-            st->frozen_at[r][j] = it;
-            st->frozen_rr[r][j] = zn * zn * rr_new;
-        } else {
-            live = 1;
-        }
-    }
-    // also the barrier between every thread's reads of rr and iter and
-    // thread 0's writes below
-    const int left = __syncthreads_count(live);
-    if (j == 0) {
-        st->iter[r] = it;
-        st->beta[r] = beta;
-        st->rr[r] = rr_new;
-        st->alpha_old[r] = st->alpha[r];
-        if (!left) st->skip[r] = 1;
-    }
+    alpha_stage<kBlock>(a, blockIdx.x, lds);
+}
+
+__global__ __launch_bounds__(kBlock) void k_ms_beta(ProArgs a)
+{
+    __shared__ double lds[4];
+    beta_stage<kBlock>(a, blockIdx.x, lds);
 }
 
 // Shift update, FP64 fields.  Fields: r [nrhs], p and x [nshift][nrhs].
@@ -229,7 +145,7 @@ size_t mscg_ws_bytes(const Lat &L, int nrhs, int nshift)
     WsCarve c{nullptr, 0, 0};
     size_t F = field_bytes(P_F64, L.V);
     c.take(sizeof(MState));
-    c.take(sizeof(double) * 2 * nrhs * site_blocks(L));
+    c.take(sizeof(double) * 2 * nrhs * part_stride(L));
     c.take(sizeof(double) * 4 * NR);
     c.take(F * nrhs);            // r
     c.take(F * nrhs);            // t
@@ -286,11 +202,11 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
 {
     const int R = b.nrhs;
     const int nblk = site_blocks(L);
-    const int npart = stencil_partials(L, P_F64, R);   // slots the iteration stencils fill
+    const int pstr = part_stride(L);
     WsCarve c{ws, 0, ws_bytes};
     size_t F = field_bytes(P_F64, L.V);
     MState *S = (MState *)c.take(sizeof(MState));
-    double *partials = (double *)c.take(sizeof(double) * 2 * R * nblk);
+    double *partials = (double *)c.take(sizeof(double) * 2 * R * pstr);
     double *red = (double *)c.take(sizeof(double) * 4 * NR);
     Fld r{c.take(F * R), nullptr, P_F64, R};
     Fld t{c.take(F * R), nullptr, P_F64, R};
@@ -331,6 +247,9 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
     B.out = r.d;
     B.shift = s0;
     B.alpha = S->alpha;
+    const int npart = stencil_partials(L, P_F64, R);
+    const ProArgs pa{PRO_ALPHA, npart, pstr, partials, S, nullptr, 0.0};
+    const ProArgs pb{PRO_BETA, npart, pstr, partials, S, nullptr, 0.0};
 
     const int check = prm->check_every > 0 ? prm->check_every : 10;
     int it = 0;
@@ -348,11 +267,11 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
             prof.pair(OVL_K_STENCIL, &v0, &v1);
             OVL_HIP(launch_wilson(L, P_F64, W_NORM, true, A, st, v0, v1));
             prof.pair(OVL_K_SCALAR, &v0, &v1);
-            launch_k(k_ms_alpha, dim3(R), dim3(kBlock), st, v0, v1, S, (const double *)partials, nblk, npart);
+            launch_k(k_ms_alpha, dim3(R), dim3(kBlock), st, v0, v1, pa);
             prof.pair(OVL_K_STENCIL, &v0, &v1);
             OVL_HIP(launch_wilson(L, P_F64, W_RUPDATE, true, B, st, v0, v1));
             prof.pair(OVL_K_SCALAR, &v0, &v1);
-            launch_k(k_ms_beta, dim3(R), dim3(kBlock), st, v0, v1, S, (const double *)partials, nblk, npart);
+            launch_k(k_ms_beta, dim3(R), dim3(kBlock), st, v0, v1, pb);
             prof.pair(OVL_K_UPDATE, &v0, &v1);
             launch_k(k_ms_update<P_F64>, sgrid, dim3(kBlock), st, v0, v1, L.g, L.nb, (const MState *)S,
                      (const void *)r.d, (const float *)nullptr, pfl.d, (float *)nullptr, x.d, (float *)nullptr, R);

@@ -9,6 +9,7 @@
 #pragma once
 
 #include "device.h"
+#include "scalars.h"
 
 namespace ovl {
 
@@ -44,7 +45,7 @@ struct WArgs {
     const double *alpha;    // W_RUPDATE(0): alpha per RHS (device)
     double *partials;       // [quantity][nrhs][nblk]
     const int *skip;        // per-RHS flag: block exits if skip[r] != 0 (may be null)
-    int nblk;               // partial-sum slots per RHS and quantity (2 * blocks per parity)
+    int nblk;               // row stride of partials (part_stride)
     int nrhs;
     int kr;                 // streaming form: K = 2^kr consecutive lanes hold K RHS of one
                             // site (set by launch_wilson)
@@ -333,7 +334,7 @@ __device__ __forceinline__ void hops_mu_lds(const Geom &g, const SpinorRef<PREC>
 // and spill.
 template <int PREC, int MODE, bool G5>
 __device__ __forceinline__ void site_out(const WArgs &a, int r, int rb, int lo, int p, int i, double shift_r,
-                                         double rin_s, cplx<typename Real<PREC>::T> o[4][3],
+                                         double rin_s, double alpha, cplx<typename Real<PREC>::T> o[4][3],
                                          typename Real<PREC>::T dn2, double &q0, double &q1, bool live = true)
 {
     using T = typename Real<PREC>::T;
@@ -376,7 +377,7 @@ __device__ __forceinline__ void site_out(const WArgs &a, int r, int rb, int lo, 
     if (MODE == W_RUPDATE || MODE == W_RUPDATE0) {
         cplx<T> rv[4][3];
         spinor_ref<PREC>(a.rin, a.rin_sc, g.S, rb).load_nt(p, i + lo, rv);
-        const T al = (T)a.alpha[r];
+        const T al = (T)alpha;
         T n0 = 0;
 #pragma unroll
         for (int s = 0; s < 4; s++)
@@ -423,22 +424,50 @@ __device__ __forceinline__ T diag_minus_half(cplx<T> acc[4][3], const cplx<T> d[
     return dn2;
 }
 
+// Modes whose launches may carry a scalar stage (pro, a kernel argument of its
+// own: a larger WArgs made the streaming kernels spill).  Beta then replaces
+// the shift of W_SNORM, alpha that of W_RUPDATE(0).
+template <int MODE>
+constexpr bool kPro = MODE == W_SNORM || MODE == W_RUPDATE || MODE == W_RUPDATE0;
+
+// The shift and alpha of RHS r's sites: given, or formed from the previous
+// launch's partial sums; false if the RHS takes no part.
+template <int MODE, int NT>
+__device__ __forceinline__ bool site_scalars(const WArgs &a, const ProArgs &pro, int r, double *lds, double *shift,
+                                             double *alpha)
+{
+    constexpr bool kShift = MODE == W_SHIFT || MODE == W_RUPDATE || MODE == W_RESNORM || MODE == W_SNORM;
+    *shift = kShift && !(MODE == W_SNORM && pro.kind) ? (a.shiftv ? a.shiftv[r] : a.shift) : 0.0;
+    *alpha = 0.0;
+    if (MODE == W_RUPDATE || MODE == W_RUPDATE0) {
+        if (!pro.kind) *alpha = a.alpha[r];
+        else if (!pro_alpha<NT>(pro, r, lds, alpha)) return false;
+    }
+    if (MODE == W_SNORM && pro.kind) *shift = pro_beta<NT>(pro, r, lds);
+    return true;
+}
+
 template <int PREC, int MODE, bool G5>
-__global__ __launch_bounds__(kBlock) void k_wilson(WArgs a)
+__global__ __launch_bounds__(kBlock) void k_wilson(WArgs a, ProArgs pro)
 {
     using T = typename Real<PREC>::T;
     __shared__ double lds[8];
     // Blocks are ordered (site block, RHS) with the RHS fastest, so the nrhs
     // blocks covering the same sites run back to back on one XCD and share
     // each link through its L2.
-    const int lbr = xcd_remap(blockIdx.x, gridDim.x);
+    // With a scalar stage the launch's first nrhs blocks run it (scalars.h).
+    const int first = kPro<MODE> && pro.kind ? a.nrhs : 0;
+    if (kPro<MODE> && (int)blockIdx.x < first) {
+        pro_stage<kBlock>(pro, blockIdx.x, lds);
+        return;
+    }
+    const int lbr = xcd_remap(blockIdx.x - first, gridDim.x - first);
     const int r = lbr % a.nrhs;
     const int lb = lbr / a.nrhs;
-    const int nb = gridDim.x / a.nrhs;   // site blocks (both parities)
     if (a.skip && a.skip[r]) return;
-    // the epilogue's shift, read once up front (a uniform scalar)
-    constexpr bool kShift = MODE == W_SHIFT || MODE == W_RUPDATE || MODE == W_RESNORM || MODE == W_SNORM;
-    const double shift_r = kShift ? (a.shiftv ? a.shiftv[r] : a.shift) : 0.0;
+    // the epilogue's shift and alpha, read (or formed) once up front (uniform scalars)
+    double shift_r, alpha_r;
+    if (!site_scalars<MODE, kBlock>(a, pro, r, lds, &shift_r, &alpha_r)) return;
     // the residual norm's scale of rin, likewise read once up front (a load
     // left inside the epilogue behind the null test made the compiler keep far
     // more values live across the hops and spill)
@@ -466,14 +495,14 @@ __global__ __launch_bounds__(kBlock) void k_wilson(WArgs a)
         cplx<T> d[4][3];
         in.load(p, i, d);
         const T dn2 = diag_minus_half(acc, d, (T)a.diag);
-        site_out<PREC, MODE, G5>(a, r, r, 0, p, i, shift_r, rin_s, acc, dn2, q0, q1);
+        site_out<PREC, MODE, G5>(a, r, r, 0, p, i, shift_r, rin_s, alpha_r, acc, dn2, q0, q1);
     }
     if (MODE == W_NORM || MODE == W_SNORM || MODE == W_RUPDATE || MODE == W_RUPDATE0 || MODE == W_RESNORM) {
         double t0 = block_sum(q0, lds);
-        if (threadIdx.x == 0) a.partials[(size_t)r * nb + lb] = t0;
+        if (threadIdx.x == 0) a.partials[(size_t)r * a.nblk + lb] = t0;
         if (MODE == W_NORM) {
             double t1 = block_sum(q1, lds + 4);
-            if (threadIdx.x == 0) a.partials[(size_t)(a.nrhs + r) * nb + lb] = t1;
+            if (threadIdx.x == 0) a.partials[(size_t)(a.nrhs + r) * a.nblk + lb] = t1;
         }
     }
 }
@@ -527,9 +556,8 @@ __device__ __forceinline__ void tback_add(cplx<T> acc[4][3], const cplx<T> w[2][
 // whose rows do not tile 256 sites (stream_threads).
 // Lanes of an RHS beyond nrhs (last tile) or of a finished RHS (skip) take
 // part in the walk and the barriers but store nothing and add no norms.
-// Partial sums: for each RHS q of the tile, slot lb holds the block's sum and
-// the block zeroes the slots lb + m*nbt (m >= 1) below a.nblk, so all 2*nb
-// slots per RHS are valid.
+// Partial sums: for each RHS q of the tile, slot lb holds the block's sum
+// (stencil_partials slots in all).
 // TILED builds take the RHS tile from a.kr; the others have K = 1 at compile
 // time, so the RHS index and everything derived from it stay block-uniform
 // (scalar registers).
@@ -547,7 +575,6 @@ __global__ __launch_bounds__(NT, WPE) void k_wilson_ts(WArgs a)
     const int lbr = xcd_remap(blockIdx.x, gridDim.x);
     const int rt = lbr % ntile;
     const int lb = lbr / ntile;
-    const int nbt = gridDim.x / ntile;   // blocks per RHS tile
     const int rq = rt * K + (threadIdx.x & (K - 1));
     const int r = rq < a.nrhs ? rq : a.nrhs - 1;   // idle lanes walk the tile's last RHS
     const bool live = rq < a.nrhs && !(a.skip && a.skip[rq]);
@@ -562,6 +589,7 @@ __global__ __launch_bounds__(NT, WPE) void k_wilson_ts(WArgs a)
     // left inside the epilogue behind the null test made the compiler keep far
     // more values live across the hops and spill)
     const double rin_s = MODE == W_RESNORM && a.rin_scale ? a.rin_scale[r] : 1.0;
+    const double alpha_r = MODE == W_RUPDATE || MODE == W_RUPDATE0 ? a.alpha[r] : 0.0;
     const int L0 = g.L[0], L1 = g.L[1], L2 = g.L[2], L3 = g.L[3];
     const int NS = NT >> kr;
     const int nsb = L1 * L2 * L3 / NS;
@@ -648,7 +676,7 @@ __global__ __launch_bounds__(NT, WPE) void k_wilson_ts(WArgs a)
 #pragma unroll
                 for (int c = 0; c < 3; c++) acc[s][c] = acc[s][c] + f[s][c];
         }
-        site_out<PREC, MODE, G5>(a, r, rb, lo, p, i, shift_r, rin_s, acc, dn2, q0, q1, !TILED || live);
+        site_out<PREC, MODE, G5>(a, r, rb, lo, p, i, shift_r, rin_s, alpha_r, acc, dn2, q0, q1, !TILED || live);
         if (STAGE) {
             // every thread has read this slice's copy: replace it by the next slice
             __syncthreads();
@@ -662,22 +690,11 @@ __global__ __launch_bounds__(NT, WPE) void k_wilson_ts(WArgs a)
         constexpr int nq = MODE == W_NORM ? 2 : 1;
         double t0s = block_sum_k<NT / 64>(q0, lds, kr);
         double t1s = nq == 2 ? block_sum_k<NT / 64>(q1, lds + (NT / 64) * 8, kr) : 0.0;
-        // thread q of the first K holds RHS rt*K + q's sums; the zeroed slots
-        // of the tile's RHS are spread over the block's threads
-        __shared__ double sums[2][8];
-        if (threadIdx.x < K) {
-            sums[0][threadIdx.x] = t0s;
-            sums[1][threadIdx.x] = t1s;
-        }
-        __syncthreads();
-        const int nz = (a.nblk - 1 - lb) / nbt + 1;   // slots lb + m*nbt below nblk
-        for (int idx = threadIdx.x; idx < K * nz; idx += NT) {
-            const int q = idx % K, m = idx / K;
-            const int rr = rt * K + q;
-            if (rr >= a.nrhs || (a.skip && a.skip[rr])) continue;
-            const size_t slot = (size_t)lb + (size_t)m * nbt;
-            a.partials[(size_t)rr * a.nblk + slot] = m == 0 ? sums[0][q] : 0.0;
-            if (nq == 2) a.partials[(size_t)(a.nrhs + rr) * a.nblk + slot] = m == 0 ? sums[1][q] : 0.0;
+        // thread q of the first K holds RHS rt*K + q's sums
+        const int rr = TILED ? rt * K + (int)threadIdx.x : r;
+        if ((int)threadIdx.x < K && (!TILED || (rr < a.nrhs && !(a.skip && a.skip[rr])))) {
+            a.partials[(size_t)rr * a.nblk + lb] = t0s;
+            if (nq == 2) a.partials[(size_t)(a.nrhs + rr) * a.nblk + lb] = t1s;
         }
     }
 }

@@ -1,6 +1,9 @@
-// Launch of the Wilson stencil kernels (wilson.h): blocks of 256 sites (192
-// for the streaming form on some extents), ordered (site block, RHS) and
-// spread over the XCDs by the kernel itself.
+// Launch of the Wilson stencil kernels (wilson.h, wilson_tile.h): blocks of 256
+// sites (192 for the streaming form on some extents, up to 512 for the tile
+// form), ordered (site block, RHS) and spread over the XCDs by the kernel itself.
+#include <algorithm>
+#include <cmath>
+
 #include "internal.h"
 
 namespace ovl {
@@ -93,6 +96,58 @@ static StencilShape stencil_shape_ts(const Lat &L, int ts, int nrhs)
     return sh;
 }
 
+// The tile of a lattice's tile form.  Below 131072 sites tiles give a CU too
+// little to overlap (FP64 D_W at 16^4: 14.5 us with one site per thread, 13.6
+// with tiles; 28x14^2x16: 21 and 27) and there are none.  Rows of x3 stay whole
+// up to 32 sites (a row is then whole 128-byte lines or nearly so); the other
+// extents are divisors of the lattice's, and the choice follows a sweep over
+// eight lattices of 131072 to 663552 sites: x2, whose neighbours are the nearest
+// blocks, at least 2 (48x22^3: 115 us with 4x2x2x22, 137 with 4x2x1x22), time
+// about 4, x1 least of all; and blocks that fill the last round of a CU's 512
+// threads (40x18^3: 47 us at 2.8 rounds, 50 at 2.1).  The best tiles then take
+// 0.67 to 0.88 of the one-site form's time, one field or three; 48x22^3 with
+// three fields alone is 2% behind.
+constexpr int64_t kTileSites = 512 * 256;
+
+Tile pick_tile(const int E[4], int64_t V)
+{
+    Tile best{};
+    if (V < kTileSites) return best;
+    int t3 = 0;
+    for (int d = std::min(32, E[3]); d > 0 && !t3; d--)
+        if (E[3] % d == 0 && (d == E[3] || d % 8 == 0)) t3 = d;
+    for (int d = std::min(32, E[3]); d > 0 && !t3; d--)
+        if (E[3] % d == 0) t3 = d;
+    double least = 1e300;
+    for (int nt : {512, 256})
+        for (int t2 = 1; t2 <= std::min(8, E[2]) && t2 * t3 <= nt; t2++) {
+            if (E[2] % t2) continue;
+            for (int t1 = 1; t1 <= std::min(8, E[1]) && t1 * t2 * t3 <= nt; t1++) {
+                if (E[1] % t1) continue;
+                for (int t0 = 1; t0 <= std::min(8, E[0]) && t0 * t1 * t2 * t3 <= nt; t0++) {
+                    if (E[0] % t0 || 2 * t0 * t1 * t2 * t3 <= nt) continue;
+                    const Tile t{{t0, t1, t2, t3}, {E[0] / t0, E[1] / t1, E[2] / t2, E[3] / t3}, 0, 0, 0, nt};
+                    const double rounds = (double)t.N[0] * t.N[1] * t.N[2] * t.N[3] * nt / (256 * 512);
+                    const double cost = (3.0 + 1.5 / t0 + 0.05 * t0 + 0.7 / t1 + 2.5 / t2) *
+                                        std::sqrt(std::ceil(rounds) / rounds);
+                    if (cost < least) {
+                        least = cost;
+                        best = t;
+                    }
+                }
+            }
+        }
+    auto inverse = [](int d) { return (unsigned)(((1u << 20) + d - 1) / d); };
+    if (best.nt) {
+        best.m3 = inverse(best.T[3]);
+        best.m2 = inverse(best.T[2]);
+        best.m1 = inverse(best.T[1]);
+    }
+    return best;
+}
+
+static int tile_count(const Tile &t) { return t.N[0] * t.N[1] * t.N[2] * t.N[3]; }
+
 // 48-bit fields take the FP64 length, halved while the launch has fewer than
 // 512 blocks: their staged build runs two waves per SIMD (below), which needs
 // two blocks per CU (at 32^3x64: 16 slices and 512 blocks, the mixed solver's
@@ -102,37 +157,62 @@ static StencilShape stencil_shape_ts(const Lat &L, int ts, int nrhs)
 StencilShape stencil_shape(const Lat &L, int prec, int nrhs)
 {
     const int ts = (prec == P_F64 || prec == P_F48) && L.g.Ts64 > 0 ? L.g.Ts64 : L.g.Ts;
-    if (ts <= 0 || prec == P_F16S) return StencilShape{};
+    if (ts <= 0 || prec == P_F16S) {
+        StencilShape sh{};
+        if (prec == P_F64 || prec == P_F48) sh.tile = L.tile;
+        return sh;
+    }
     StencilShape sh = stencil_shape_ts(L, ts, nrhs);
     while (prec == P_F48 && sh.ts % 2 == 0 && (int64_t)sh.blocks_per_tile * sh.ntile < 512)
         sh = stencil_shape_ts(L, sh.ts / 2, nrhs);
     return sh;
 }
 
+int stencil_partials(const Lat &L, int prec, int nrhs)
+{
+    const StencilShape sh = stencil_shape(L, prec, nrhs);
+    return sh.ts > 0 ? sh.blocks_per_tile : sh.tile.nt ? tile_count(sh.tile) : 2 * L.nb;
+}
+
+int part_stride(const Lat &L)
+{
+    return std::max(2 * L.nb, L.tile.nt ? tile_count(L.tile) : 0);
+}
+
+// Every block of a carrying launch adds up all of the previous one's partial
+// sums: cheap up to the 512 blocks of 16^3x32, but their reads grow with the
+// square of the lattice
+bool carries_scalars(const Lat &L, int prec, int nrhs)
+{
+    return stencil_shape(L, prec, nrhs).ts == 0 && stencil_partials(L, prec, nrhs) <= 512;
+}
+
 template <int PREC>
-static void wilson_dispatch(int mode, bool g5, dim3 grid, const WArgs &a, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
+static void wilson_dispatch(int mode, bool g5, dim3 grid, const WArgs &a, const ProArgs &pro, hipStream_t st,
+                            hipEvent_t e0, hipEvent_t e1)
 {
     const dim3 b(kBlock);
     if (g5) {
         switch (mode) {
-        case W_PLAIN: launch_k(k_wilson<PREC, W_PLAIN, true>, grid, b, st, e0, e1, a); break;
-        case W_NORM: launch_k(k_wilson<PREC, W_NORM, true>, grid, b, st, e0, e1, a); break;
-        case W_SHIFT: launch_k(k_wilson<PREC, W_SHIFT, true>, grid, b, st, e0, e1, a); break;
-        case W_RUPDATE: launch_k(k_wilson<PREC, W_RUPDATE, true>, grid, b, st, e0, e1, a); break;
-        case W_RUPDATE0: launch_k(k_wilson<PREC, W_RUPDATE0, true>, grid, b, st, e0, e1, a); break;
-        case W_SNORM: launch_k(k_wilson<PREC, W_SNORM, true>, grid, b, st, e0, e1, a); break;
-        default: launch_k(k_wilson<PREC, W_RESNORM, true>, grid, b, st, e0, e1, a); break;
+        case W_PLAIN: launch_k(k_wilson<PREC, W_PLAIN, true>, grid, b, st, e0, e1, a, pro); break;
+        case W_NORM: launch_k(k_wilson<PREC, W_NORM, true>, grid, b, st, e0, e1, a, pro); break;
+        case W_SHIFT: launch_k(k_wilson<PREC, W_SHIFT, true>, grid, b, st, e0, e1, a, pro); break;
+        case W_RUPDATE: launch_k(k_wilson<PREC, W_RUPDATE, true>, grid, b, st, e0, e1, a, pro); break;
+        case W_RUPDATE0: launch_k(k_wilson<PREC, W_RUPDATE0, true>, grid, b, st, e0, e1, a, pro); break;
+        case W_SNORM: launch_k(k_wilson<PREC, W_SNORM, true>, grid, b, st, e0, e1, a, pro); break;
+        default: launch_k(k_wilson<PREC, W_RESNORM, true>, grid, b, st, e0, e1, a, pro); break;
         }
     } else {
-        launch_k(k_wilson<PREC, W_PLAIN, false>, grid, b, st, e0, e1, a);
+        launch_k(k_wilson<PREC, W_PLAIN, false>, grid, b, st, e0, e1, a, pro);
     }
 }
 
 hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hipStream_t st, hipEvent_t e0,
-                         hipEvent_t e1)
+                         hipEvent_t e1, const ProArgs *pro)
 {
+    const ProArgs pa = pro ? *pro : ProArgs{};
     a.g = L.g;
-    a.nblk = 2 * L.nb;
+    a.nblk = part_stride(L);
     a.kr = 0;
     if (prec == P_F32 && mode == W_PLAIN && L.g.Mfma && a.nrhs >= 2) {
         // the matrix-core form: events as markers around its launch
@@ -149,7 +229,7 @@ hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hip
         // time-streaming form (FP64, 48-bit, FP32): blocks_per_tile blocks per RHS
         // tile; the FP16 stencil keeps one site per thread, which measured
         // faster
-        if (sh.blocks_per_tile > a.nblk) return hipErrorInvalidConfiguration;
+        if (sh.blocks_per_tile > a.nblk || pa.kind) return hipErrorInvalidConfiguration;
         a.kr = sh.kr;
         if (prec == P_F48) a.g.Ts64 = sh.ts;   // the kernel reads its length from there
         dim3 grid((unsigned)sh.blocks_per_tile * sh.ntile);
@@ -158,11 +238,16 @@ hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hip
         else wilson_ts_dispatch<P_F32>(mode, g5, grid, sh.nt, a, st, e0, e1);
         return hipGetLastError();
     }
-    dim3 grid(2 * L.nb * a.nrhs);
-    if (prec == P_F64) wilson_dispatch<P_F64>(mode, g5, grid, a, st, e0, e1);
-    else if (prec == P_F48) wilson_dispatch<P_F48>(mode, g5, grid, a, st, e0, e1);
-    else if (prec == P_F32) wilson_dispatch<P_F32>(mode, g5, grid, a, st, e0, e1);
-    else wilson_dispatch<P_F16S>(mode, g5, grid, a, st, e0, e1);
+    const int extra = pa.kind ? a.nrhs : 0;   // blocks of the scalar stage
+    if (sh.tile.nt) {
+        dim3 grid((unsigned)tile_count(sh.tile) * a.nrhs + extra);
+        return launch_wilson_tile(prec, mode, g5, grid, a, sh.tile, pa, st, e0, e1);
+    }
+    dim3 grid(2 * L.nb * a.nrhs + extra);
+    if (prec == P_F64) wilson_dispatch<P_F64>(mode, g5, grid, a, pa, st, e0, e1);
+    else if (prec == P_F48) wilson_dispatch<P_F48>(mode, g5, grid, a, pa, st, e0, e1);
+    else if (prec == P_F32) wilson_dispatch<P_F32>(mode, g5, grid, a, pa, st, e0, e1);
+    else wilson_dispatch<P_F16S>(mode, g5, grid, a, pa, st, e0, e1);
     return hipGetLastError();
 }
 
