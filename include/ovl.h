@@ -187,7 +187,9 @@ typedef struct {
     int32_t mode;            /* enum ovl_solve_mode */
     double reliable_delta;   /* mixed: FP64 residual replacement when ||r|| has
                                 fallen by this factor since the last one */
-    int32_t check_every;     /* iterations between host convergence polls */
+    int32_t check_every;     /* iterations between host convergence polls (of
+                                the plain form; the blocked ones poll at
+                                block ends) */
     int32_t refine;          /* mixed: verify each shift in FP64 and refine
                                 those above tol (1) or only report (0) */
     int32_t verify;          /* FP64 mode: also compute every shift's FP64 true
@@ -197,10 +199,14 @@ typedef struct {
                                 1 every class, 2 the stencils only (each timed
                                 kernel costs a little; 2 keeps the cost to the
                                 dominant class); 0 (default) none */
-    int32_t block;           /* FP64 mode: 0 updates every shifted vector in every
-                                iteration; m = 1..OVL_MAX_BLOCK keeps the last m residuals
+    int32_t block;           /* FP64 mode: m = 1..OVL_MAX_BLOCK keeps the last m residuals
                                 and updates each shifted vector once per m
                                 iterations (same iterates, fewer vector passes).
+                                0 does so with up to 16 residuals where only
+                                the weighted sum is asked for (4 shifts or
+                                more, no verify); otherwise it updates every
+                                shifted vector in every iteration (the plain
+                                form, the least workspace).
                                 Mixed mode: block length of the FP32 phase,
                                 0 meaning 32 */
     double sloppy_below;     /* mixed: iterate in FP64 (blocked, accumulating the

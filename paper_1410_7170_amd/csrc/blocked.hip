@@ -22,18 +22,6 @@
 
 namespace ovl {
 
-__global__ void k_blk_reset(Blk *bk, const MState *st, int nrhs, int nshift)
-{
-    int r = blockIdx.x, j = threadIdx.x;
-    if (r < nrhs && j < NS) {
-        bk->P[r][j] = 1.0;
-        bk->XP[r][j] = 0.0;
-        for (int i = 0; i <= MB; i++) bk->C[r][j][i] = bk->X[r][j][i] = 0.0;
-        bk->inblk[r][j] = (j < nshift) ? st->act[r][j] : 0;
-        if (j == 0) bk->t[r] = 0;
-    }
-}
-
 // Element traits of the solver's vector fields: FP64 fields are arrays of
 // complex128 (12 per site and parity), FP32 fields of float4 (two complex,
 // 6 per site and parity), 48-bit fields hold two complex per element in two
@@ -164,7 +152,8 @@ struct El<P_F32> {
 // p0 = r_new + beta p0 on the RHS of this iteration (run_c; also one that it
 // finishes, whose p0 nothing reads, or pauses).  With the beta stage aboard
 // (pro.kind) the first block of each RHS runs it and the others form beta
-// themselves.  Non-temporal loads: FP64 214 -> 194 us, FP32 89 -> 86 us
+// themselves.  The grid's z deals out a site's elements (elem_split; 16x12x8x6:
+// 9.6 us with one thread for all twelve).  Non-temporal loads: FP64 214 -> 194 us, FP32 89 -> 86 us
 // at 32^3x64 (a non-temporal store as well made it slower).
 template <int PS>
 __global__ __launch_bounds__(kBlock) void k_base_p(Geom g, int nb, const MState *st, const void *rnv, void *p0v,
@@ -175,15 +164,14 @@ __global__ __launch_bounds__(kBlock) void k_base_p(Geom g, int nb, const MState 
     const int r = blockIdx.y;
     const int b = (int)blockIdx.x - (pro.kind ? 1 : 0);
     if (b < 0) {
-        beta_stage<kBlock>(pro, r, lds);
+        if (blockIdx.z == 0) beta_stage<kBlock>(pro, r, lds);
         return;
     }
     if (!st->run_c[r]) return;
     const double be = pro.kind ? pro_beta<kBlock>(pro, r, lds) : st->beta[r];
     const int p = b / nb, i = (b % nb) * kBlock + threadIdx.x;
     if (i >= g.Vh) return;
-#pragma unroll
-    for (int e = 0; e < E::N; e++) {
+    for (int e = blockIdx.z; e < E::N; e += gridDim.z) {
         double ar[E::C], ai[E::C], qr[E::C], qi[E::C];
         const typename E::O o = E::off(g.S, p, i, e);
         const size_t k = (size_t)r * E::W * g.S;
@@ -211,7 +199,10 @@ struct RingPtrs {
 // PIN48, in 48 bits), rounded to FP32 as a conversion would round them.  xzero (x mode): the x_j of shifts
 // j < xzero start at zero; the pass writes x_j = dx_j for the block's shifts
 // and zeros for the others below xzero (for every one of an RHS with no
-// iteration in the block).  The block's shifts all lie below xzero.
+// iteration in the block).  The block's shifts all lie below xzero.  xo: the
+// x_j of systems j < xo (a base of its own) are not kept, the first x field is
+// system xo's.  The grid's z deals out a site's elements (elem_split): at
+// 16x12x8x6 a pass with one thread for all twelve took 90 us.
 // The 48-bit 16-slot build is held to three waves per SIMD (its residuals
 // take 6 registers a slot; left alone it takes 173 and two waves, 3.25 ms a
 // pass at 32^3x64 against 2.94-3.02 ms at three waves with a 28-byte spill;
@@ -220,7 +211,7 @@ struct RingPtrs {
 template <int PS, int MBT, bool PIN48 = false>
 __global__ __launch_bounds__(kBlock, PS == P_F48 && MBT <= 16 ? 3 : 1) void k_blk_pass(Geom g, int nb, const MState *st, const Blk *bk, RingPtrs ring,
                                                      ShiftWeights w, void *pfv, double2 *xf, double2 *y, int nrhs,
-                                                     int first, const void *pin, int xzero)
+                                                     int first, const void *pin, int xzero, int xo)
 {
     using E = El<PS>;
     using V = typename E::V;
@@ -235,29 +226,31 @@ __global__ __launch_bounds__(kBlock, PS == P_F48 && MBT <= 16 ? 3 : 1) void k_bl
     const int p = b / nb, i = (b % nb) * kBlock + threadIdx.x;
     const size_t site64 = (size_t)p * 12 * g.S + i;
     auto zero_x = [&](int j) {
-        double2 *xp = xf + ((size_t)j * nrhs + r) * F64 + site64;
+        if (j < xo) return;
+        double2 *xp = xf + ((size_t)(j - xo) * nrhs + r) * F64 + site64;
 #pragma unroll
         for (int c = 0; c < 12; c++) xp[(size_t)c * g.S] = make_double2(0.0, 0.0);
     };
     const bool xz = xzero > 0 && xf;
-    const int nzs = xzero < st->nshift ? xzero : st->nshift;
+    const int nzs = blockIdx.z ? 0 : xzero < st->nshift ? xzero : st->nshift;
     if (T == 0) {
         if (xz && i < g.Vh)
             for (int j = 0; j < nzs; j++) zero_x(j);
         return;
     }
-    if (threadIdx.x == 0) {
-        int n = 0;
-        for (int j = 0; j < st->nshift; j++)
-            if (bk->inblk[r][j]) {
-                sj[n] = j;
-                sact[n] = st->act[r][j];
-                sP[n] = bk->P[r][j];
-                sXP[n] = bk->XP[r][j];
-                sW[n] = w.w[j];
-                n++;
-            }
-        sn = n;
+    if (threadIdx.x < 64) {   // the block's shifts, in order
+        const int j = threadIdx.x;
+        const bool in = j < st->nshift && bk->inblk[r][j < NS ? j : 0];
+        const unsigned long long m = __ballot(in);
+        if (in) {
+            const int n = __popcll(m & ((1ull << j) - 1));
+            sj[n] = j;
+            sact[n] = st->act[r][j];
+            sP[n] = bk->P[r][j];
+            sXP[n] = bk->XP[r][j];
+            sW[n] = w.w[j];
+        }
+        if (j == 0) sn = __popcll(m);
     }
     __syncthreads();
     const int n = sn;
@@ -273,7 +266,7 @@ __global__ __launch_bounds__(kBlock, PS == P_F48 && MBT <= 16 ? 3 : 1) void k_bl
             if (!bk->inblk[r][j]) zero_x(j);
     if (n == 0) return;
     const size_t FS = (size_t)E::W * g.S;   // sloppy field, in 16-byte units
-    for (int e = 0; e < E::N; e++) {
+    for (int e = blockIdx.z; e < E::N; e += gridDim.z) {
         const typename E::O off = E::off(g.S, p, i, e);
         // the block's residuals stay in their storage precision in registers
         // (4 VGPRs per slot, 6 for 48-bit fields) and are widened where they
@@ -292,8 +285,9 @@ __global__ __launch_bounds__(kBlock, PS == P_F48 && MBT <= 16 ? 3 : 1) void k_bl
         // always in flight while the previous shift computes
         auto pfield = [&](int q) { return ((size_t)sj[q] * nrhs + r) * FS; };
         auto xptr = [&](int q) {
-            return xf + ((size_t)sj[q] * nrhs + r) * F64 + site64 + (size_t)(e * E::C) * g.S;
+            return xf + ((size_t)(sj[q] - xo) * nrhs + r) * F64 + site64 + (size_t)(e * E::C) * g.S;
         };
+        auto keep = [&](int q) { return sj[q] >= xo; };
         auto pload = [&](int q) -> V {
             if (PS == P_F32 && PIN48 && pin) {
                 using E48 = El<P_F48>;
@@ -318,7 +312,8 @@ __global__ __launch_bounds__(kBlock, PS == P_F48 && MBT <= 16 ? 3 : 1) void k_bl
         double2 xcur[E::C];
         if (xf) {
 #pragma unroll
-            for (int c = 0; c < E::C; c++) xcur[c] = xz ? make_double2(0.0, 0.0) : xptr(0)[(size_t)c * g.S];
+            for (int c = 0; c < E::C; c++)
+                xcur[c] = xz || !keep(0) ? make_double2(0.0, 0.0) : xptr(0)[(size_t)c * g.S];
         }
         for (int q = 0; q < n; q++) {
             V pnext = pcur;
@@ -328,7 +323,7 @@ __global__ __launch_bounds__(kBlock, PS == P_F48 && MBT <= 16 ? 3 : 1) void k_bl
                 if (xf) {
 #pragma unroll
                     for (int c = 0; c < E::C; c++)
-                        xnext[c] = xz ? make_double2(0.0, 0.0) : xptr(q + 1)[(size_t)c * g.S];
+                        xnext[c] = xz || !keep(q + 1) ? make_double2(0.0, 0.0) : xptr(q + 1)[(size_t)c * g.S];
                 }
             }
             double pre[E::C], pim[E::C];
@@ -357,10 +352,12 @@ __global__ __launch_bounds__(kBlock, PS == P_F48 && MBT <= 16 ? 3 : 1) void k_bl
                 }
             if (sact[q] || first) E::st(pfv, pfield(q), off, E::put(pnr, pni));
             if (xf) {
-                double2 *xp = xptr(q);
+                if (keep(q)) {
+                    double2 *xp = xptr(q);
 #pragma unroll
-                for (int c = 0; c < E::C; c++)
-                    xp[(size_t)c * g.S] = make_double2(xcur[c].x + dxr[c], xcur[c].y + dxi[c]);
+                    for (int c = 0; c < E::C; c++)
+                        xp[(size_t)c * g.S] = make_double2(xcur[c].x + dxr[c], xcur[c].y + dxi[c]);
+                }
 #pragma unroll
                 for (int c = 0; c < E::C; c++) xcur[c] = xnext[c];
             } else {
@@ -400,13 +397,14 @@ static void launch_blk_pass(int m, bool pin48, dim3 grid, hipStream_t st, hipEve
     else launch_k(k_blk_pass<PS, MB>, grid, b, st, e0, e1, a...);
 }
 
-// ring slot 0 = b, p0 = b (precision PS), and y = 0 or x_j = 0 (FP64).  The
+// ring slot 0 = b, p0 = b (precision PS; null: no p0), and y = 0 or the nx
+// x_j = 0 (FP64).  The
 // p_j (= b) are left to the first block pass, which reads b from slot 0;
 // only an RHS that is finished from the start (b = 0) gets them here.
 template <int PS>
 __global__ __launch_bounds__(kBlock) void k_blk_start(Geom g, int nb, const MState *st, const double2 *b, void *r0v,
                                                       void *p0v, void *pfv, double2 *xf, double2 *y, int nrhs,
-                                                      int nshift)
+                                                      int nshift, int nx)
 {
     using E = El<PS>;
     using V = typename E::V;
@@ -429,14 +427,13 @@ __global__ __launch_bounds__(kBlock) void k_blk_start(Geom g, int nb, const MSta
         const typename E::O o = E::off(g.S, p, i, e);
         const size_t FS = (size_t)E::W * g.S;
         E::st(r0v, rr * FS, o, v);
-        E::st(p0v, rr * FS, o, v);
+        if (p0v) E::st(p0v, rr * FS, o, v);
         if (st->skip[rr])
             for (int j = 0; j < nshift; j++) E::st(pfv, ((size_t)j * nrhs + rr) * FS, o, v);
     }
     for (int c = 0; c < 12; c++) {
         const size_t o64 = off64 + (size_t)c * g.S;
-        for (int j = 0; j < nshift; j++)
-            if (xf) xf[(size_t)j * nrhs * F64 + o64] = z;
+        for (int j = 0; xf && j < nx; j++) xf[(size_t)j * nrhs * F64 + o64] = z;
         if (!xf) y[o64] = z;
     }
 }
@@ -465,7 +462,9 @@ __global__ void k_set_rr(MState *st, const double *rr, int nrhs)
     }
 }
 
-size_t blocked_ws_bytes(const Lat &L, int nrhs, int nshift, int m, bool keep_x, int ps, bool ext_x)
+// A fresh FP64 solve whose base shift is exactly 0 forms t by recurrence (trec
+// below) and keeps no p0.
+size_t blocked_ws_bytes(const Lat &L, int nrhs, int nshift, int m, bool keep_x, int ps, bool ext_x, bool base_p_only)
 {
     WsCarve c{nullptr, 0, 0};
     const size_t F = field_bytes(P_F64, L.V), FS = field_bytes(ps, L.V);
@@ -480,11 +479,11 @@ size_t blocked_ws_bytes(const Lat &L, int nrhs, int nshift, int m, bool keep_x, 
         c.take(std::max(FS * nrhs * (m + 3), F * nrhs * nshift));
     } else {
         c.take(FS * nrhs * (m + 1));     // ring
-        c.take(FS * nrhs);               // p0
+        if (!base_p_only) c.take(FS * nrhs);   // p0
         c.take(FS * nrhs);               // t
         c.take(FS * nrhs * nshift);      // p_j
     }
-    if (keep_x && !ext_x) c.take(F * nrhs * nshift);   // x_j
+    if (keep_x && !ext_x) c.take(F * nrhs * (nshift - (base_p_only ? 1 : 0)));   // x_j
     if (keep_x || ps == P_F32) {
         c.take(F * nrhs);                // FP64 scratch (verification, residual replacement)
         c.take(F * nrhs);
@@ -510,6 +509,10 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
     const int m = o.m;
     if (m < 1 || m > MB || R > NR) return OVL_ERR_INVALID;
     if (o.reliable && !o.keep_x) return OVL_ERR_INVALID;
+    if (o.base_p_only && (PS != P_F64 || o.resume || o.rhs_shift || o.reliable || o.x_zero_shifts ||
+                          shifts[0] != 0.0 || *std::min_element(shifts, shifts + nshift) != 0.0))
+        return OVL_ERR_INVALID;
+    const int xo = o.base_p_only && o.keep_x ? 1 : 0;
     // 48-bit storage: y mode of a fresh solve on an unshifted base (the t
     // recurrence; neither p0 nor the base-direction update is needed)
     if (PS == P_F48 && (o.keep_x || o.resume || o.rhs_shift || *std::min_element(shifts, shifts + nshift) != 0.0))
@@ -536,12 +539,12 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
         t.d = ring + FS * R * (m + 2);
     } else {
         ring = (char *)c.take(FS * R * (m + 1));
-        p0.d = c.take(FS * R);
+        if (!o.base_p_only) p0.d = c.take(FS * R);
         t.d = c.take(FS * R);
         pj.d = c.take(FS * R * nshift);
     }
     Fld xs{}, s1{}, s2{};
-    if (o.keep_x) xs = {o.x_ext.d ? o.x_ext.d : c.take(F * R * nshift), nullptr, P_F64, R * nshift};
+    if (o.keep_x) xs = {o.x_ext.d ? o.x_ext.d : c.take(F * R * (nshift - xo)), nullptr, P_F64, R * (nshift - xo)};
     if (o.keep_x || PS == P_F32) {
         s1 = {c.take(F * R), nullptr, P_F64, R};
         s2 = {c.take(F * R), nullptr, P_F64, R};
@@ -579,12 +582,12 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
         }
         for (int q = 0; q < R; q++) it0[q] = h.iter[q];
     } else {
-        int rc = mscg_init_state(L, S, partials, red, b, nshift, shifts, prm, &j0, st, o.rhs_shift, o.rhs_tol);
+        int rc = mscg_init_state(L, S, partials, red, b, nshift, shifts, prm, &j0, st, o.rhs_shift, o.rhs_tol,
+                                 o.base_p_only ? 1 : 0);
         if (rc) return rc;
         k_blk_start<PS><<<sgrid, kBlock, 0, st>>>(L.g, L.nb, S, (const double2 *)b.d, slot(0), p0.d, pj.d, xf, y, R,
-                                                  nshift);
+                                                  nshift, nshift - xo);
     }
-    k_blk_reset<<<R, NS, 0, st>>>(BK, S, R, nshift);
     OVL_HIP(hipGetLastError());
     // an unshifted base system (every RHS's base shift exactly 0) needs no
     // s0 p0 term in the residual update, so that stencil does not read p0
@@ -634,8 +637,8 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
     const double sw2 = o.switch_rel * o.switch_rel;
     const bool carry = carries_scalars(L, PS, R) && !o.f16.d && !(prof.on && !prof.stencil_only);
     const ProArgs none{};
-    const ProArgs pa{PRO_ALPHA, npart, pstr, partials, S, nullptr, 0.0};
-    const ProArgs pb{PRO_BETA, npart, pstr, partials2, S, BK, sw2};
+    ProArgs pa{PRO_ALPHA, npart, pstr, partials, S, BK, 0.0, 0};
+    const ProArgs pb{PRO_BETA, npart, pstr, partials2, S, BK, sw2, 0};
     long k = 0;
     int passes = 0, replacements = 0;
     bool done = false, switched = false;
@@ -683,6 +686,7 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
                 OVL_HIP(launch_wilson(L, PS, W_NORM, true, A, st, v0, v1));
             }
             if (f16) OVL_HIP(round16(t.d));
+            pa.reset = q == 0;
             if (!carry) {
                 prof.pair(OVL_K_SCALAR, &v0, &v1);
                 launch_k(k_ms_alpha, dim3(R), dim3(kBlock), st, v0, v1, pa);
@@ -698,7 +702,7 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
             }
             if (!trec) {
                 prof.pair(OVL_K_UPDATE, &v0, &v1);
-                launch_k(k_base_p<PS>, dim3(nblk + (carry ? 1 : 0), R), dim3(kBlock), st, v0, v1, L.g, L.nb,
+                launch_k(k_base_p<PS>, dim3(nblk + (carry ? 1 : 0), R, elem_split(nblk * R, El<PS>::N)), dim3(kBlock), st, v0, v1, L.g, L.nb,
                          (const MState *)S, (const void *)slot(k + 1), p0.d, carry ? pb : none);
             }
             if (f16) OVL_HIP(round16(p0.d));
@@ -719,9 +723,8 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
         const bool pin48 = pin && o.resume->pj.prec == P_F48;
         const int xzero = passes == 0 ? o.x_zero_shifts : 0;
         prof.pair(OVL_K_UPDATE, &v0, &v1);
-        launch_blk_pass<PS>(m, pin48, sgrid, st, v0, v1, L.g, L.nb, (const MState *)S, (const Blk *)BK, rp, sw, pj.d,
-                            xf, y, R, first, pin, xzero);
-        k_blk_reset<<<R, NS, 0, st>>>(BK, S, R, nshift);
+        launch_blk_pass<PS>(m, pin48, dim3(nblk, R, elem_split(nblk * R, El<PS>::N)), st, v0, v1, L.g, L.nb,
+                            (const MState *)S, (const Blk *)BK, rp, sw, pj.d, xf, y, R, first, pin, xzero, xo);
         OVL_HIP(hipGetLastError());
         passes++;
         OVL_HIP(hipMemcpyAsync(&h, S, sizeof(MState), hipMemcpyDeviceToHost, st));
@@ -820,7 +823,7 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
             const int f = h.frozen_at[q][j] >= 0 ? h.frozen_at[q][j] : h.iter[q];
             fz[q][j] = std::max(0, f - it0[q]);
             if (stats && !o.quiet) stats->shift_iters[q][j] = f;
-            if (h.frozen_at[q][j] < 0 && !switched) status = OVL_NOT_CONVERGED;
+            if (h.frozen_at[q][j] < 0 && !switched && !(o.base_p_only && j == 0)) status = OVL_NOT_CONVERGED;
         }
     }
     if (o.iters_out)
@@ -867,7 +870,7 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
                 // an FP32 solve's first pass reads the FP64 (or 48-bit) p_j it continues
                 const double wide =
                     !fresh && PS == P_F32 ? (double)field_bytes(o.resume->pj.prec, L.V) - Fs : 0.0;
-                if (np > 0) pass += pj_io * Fs + wide + (o.keep_x ? 2.0 * np * F8 : 0.0);
+                if (np > 0) pass += pj_io * Fs + wide + (o.keep_x && j >= xo ? 2.0 * np * F8 : 0.0);
             }
         // replacement: Q x0 (768 B per site), the update stencil, the rounding into the ring
         double other = replacements * R * ((768.0 + (rmode == W_RUPDATE0 ? 960.0 : 1152.0)) * L.V + F8 + Fs);

@@ -1,6 +1,8 @@
 // Host-side declarations shared by the library's translation units.
 #pragma once
 
+#include <algorithm>
+
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -99,6 +101,10 @@ hipError_t launch_reduce(const double *partials, int nq, int nrhs, int nblk, dou
 hipError_t launch_convert(const Lat &L, Fld src, Fld dst, hipStream_t st);
 hipError_t launch_axpby(const Lat &L, double a, Fld x, double b, Fld y, hipStream_t st);
 hipError_t launch_zero(const Lat &L, Fld f, hipStream_t st);
+// Parts into which an elementwise launch of `blocks` blocks cuts its loop over n
+// independent pieces of a site (grid z): enough to give every CU four blocks,
+// at least two pieces each once there are that many (one part from 1024 blocks on)
+inline int elem_split(int blocks, int n) { return std::max(1, std::min(n, 1024 / std::max(1, blocks))); }
 // FP64 field-set kernels (outer.hip), grids of site_blocks(L) blocks:
 // partials[2][nv][nblk] of <V_f, w> for the nv fields V_f (grid.y = nv);
 // w += sgn sum_f (coef[f] + i coef[nv+f]) V_f (coef on the device);

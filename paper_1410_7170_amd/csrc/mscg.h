@@ -1,6 +1,7 @@
 // Multishift CG state and kernels shared by the FP64 and mixed solvers.
 #pragma once
 
+#include <algorithm>
 #include <map>
 #include <vector>
 
@@ -43,6 +44,9 @@ struct BlkOpts {
     const double *rhs_tol = nullptr;    // per-RHS tolerance (host), default prm->tol
     Fld x_ext{};                        // x mode: caller's FP64 x_j (field j*nrhs + r)
     int x_zero_shifts = 0;              // x mode: x_j (j < this) start at zero (set by the first pass)
+    bool base_p_only = false;           // system 0 is an unshifted base that only carries the others: the
+                                        // solve ends without it, and in x mode the x fields are those of
+                                        // systems 1..nshift-1
     int *iters_out = nullptr;           // per-RHS iteration counts (host)
     // Each RHS stops at the iteration at which |r| <= switch_rel |b| (the
     // block pass then covers the iterations it did); once no unfinished RHS
@@ -59,7 +63,11 @@ struct BlkOpts {
 // Return code of a blocked solve that stopped at switch_rel (internal).
 constexpr int kSwitched = 2;
 
-size_t blocked_ws_bytes(const Lat &L, int nrhs, int nshift, int m, bool keep_x, int ps, bool ext_x = false);
+size_t blocked_ws_bytes(const Lat &L, int nrhs, int nshift, int m, bool keep_x, int ps, bool ext_x = false,
+                        bool base_p_only = false);
+// Block length of a solve that returns sum_j w_j x_j with params.block = 0: the
+// longest up to 16 whose ring fits the plain form's workspace (0: plain form)
+inline int default_block(int nshift) { return nshift >= 4 ? std::min(16, nshift) : 0; }
 
 // Pieces of a solver workspace that callers reuse after the solve.
 struct MsScratch {
@@ -89,7 +97,7 @@ __global__ void k_ms_beta(ProArgs a);
 // the initial recurrence values.  *j0_out: index of the smallest shift.
 int mscg_init_state(const Lat &L, MState *S, double *partials, double *red, Fld b, int nshift, const double *shifts,
                     const ovl_solver_params *prm, int *j0_out, hipStream_t st, const double *rhs_shift,
-                    const double *rhs_tol);
+                    const double *rhs_tol, int jlive = 0);
 
 // Events of the profiling spans, kept for reuse across solves (per device:
 // an event belongs to the device current at its creation).

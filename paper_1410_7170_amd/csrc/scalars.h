@@ -42,6 +42,8 @@ struct MState {
     int skip[NR];          // RHS finished (every shift frozen) or failed
     int nonfinite[NR];
     int nrhs, nshift;
+    int jlive;             // an RHS is finished once systems jlive.. are frozen (1: system 0 is a base
+                           // that only carries the others)
     // reliable-update bookkeeping (mixed solver)
     double rr_ref[NR];     // |r|^2 at the last residual replacement
     int want_update[NR];
@@ -64,8 +66,9 @@ struct ProArgs {
     int pcnt, pstride;
     const double *pin;
     MState *st;
-    Blk *bk;       // PRO_BETA: block coefficients (null: none kept)
+    Blk *bk;       // block coefficients (null: none kept)
     double sw2;    // PRO_BETA: pause an RHS with |r|^2 <= sw2 |b|^2 (0: never)
+    int reset;     // PRO_ALPHA: a block's first iteration, which starts its coefficients
 };
 
 // Sum of n slots, valid in every thread of a block of NT threads.  The order
@@ -124,6 +127,13 @@ __device__ __forceinline__ void alpha_stage(const ProArgs &a, int r, double *lds
 {
     MState *st = a.st;
     const int j = threadIdx.x;
+    if (a.reset && j < NS) {
+        Blk *bk = a.bk;
+        bk->P[r][j] = 1.0;
+        bk->XP[r][j] = 0.0;
+        bk->inblk[r][j] = j < st->nshift ? st->act[r][j] : 0;
+        if (j == 0) bk->t[r] = 0;
+    }
     if (st->skip[r]) {
         if (j == 0) st->run_c[r] = 0;
         if (j < NS) st->act_cur[r][j] = 0;
@@ -199,6 +209,7 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
                 bk->C[r][j][i] = bj * c;
             }
             bk->C[r][j][t + 1] = zn;
+            bk->X[r][j][t + 1] = 0.0;
         }
         st->bj[r][j] = bj;
         st->zeta_old[r][j] = z;
@@ -208,8 +219,10 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
             st->frozen_at[r][j] = it;
             st->frozen_rr[r][j] = zn * zn * rr_new;
         } else {
-            live = 1;
+            live = j >= st->jlive;
         }
+    } else if (bk && j < st->nshift) {
+        bk->C[r][j][t + 1] = bk->X[r][j][t + 1] = 0.0;   // frozen: no part of this residual
     }
     // also the barrier between every thread's reads of rr, iter and t and
     // thread 0's writes below

@@ -55,23 +55,25 @@ __global__ __launch_bounds__(kBlock) void k_ms_beta(ProArgs a)
     beta_stage<kBlock>(a, blockIdx.x, lds);
 }
 
-// Shift update, FP64 fields.  Fields: r [nrhs], p and x [nshift][nrhs].
+// Shift update, FP64 fields.  Fields: r [nrhs], p and x [nshift][nrhs].  The
+// grid's z deals the shifts out (elem_split): at 8x4^3, 20 shifts, one block
+// after another took 20 us.
 template <int PREC>
 __global__ __launch_bounds__(kBlock) void k_ms_update(Geom g, int nb, const MState *st, const void *rf, const float *rsc,
                                                       void *pf, float *psc, void *xf, float *xsc, int nrhs)
 {
     using T = typename Real<PREC>::T;
     const int r = blockIdx.y;
-    const int ns = st->nshift;
+    const int ns = st->nshift, j0 = blockIdx.z, js = gridDim.z;
     int any = 0;
-    for (int j = 0; j < ns; j++) any |= st->act_cur[r][j];
+    for (int j = j0; j < ns; j += js) any |= st->act_cur[r][j];
     if (!any) return;
     const int b = blockIdx.x;
     const int p = b / nb, i = (b % nb) * kBlock + threadIdx.x;
     if (i >= g.Vh) return;
     cplx<T> rv[4][3];
     spinor_ref<PREC>(rf, rsc, g.S, r).load(p, i, rv);
-    for (int j = 0; j < ns; j++) {
+    for (int j = j0; j < ns; j += js) {
         if (!st->act_cur[r][j]) continue;
         const T aj = (T)st->aj[r][j], bj = (T)st->bj[r][j], zn = (T)st->zeta_new[r][j];
         auto P = spinor_ref<PREC>(pf, psc, g.S, j * nrhs + r);
@@ -167,7 +169,7 @@ static int read_state(MState &h, const MState *d, hipStream_t st)
 // initial recurrence values.  *j0_out: index of the smallest (base) shift.
 int mscg_init_state(const Lat &L, MState *S, double *partials, double *red, Fld b, int nshift, const double *shifts,
                     const ovl_solver_params *prm, int *j0_out, hipStream_t st, const double *rhs_shift,
-                    const double *rhs_tol)
+                    const double *rhs_tol, int jlive)
 {
     const int R = b.nrhs;
     int j0 = 0;
@@ -183,6 +185,7 @@ int mscg_init_state(const Lat &L, MState *S, double *partials, double *red, Fld 
     }
     h.nrhs = R;
     h.nshift = nshift;
+    h.jlive = jlive;
     for (int j = 0; j < nshift; j++) h.delta[j] = shifts[j] - shifts[j0];
     OVL_HIP(hipMemcpyAsync(S, &h, sizeof(MState), hipMemcpyHostToDevice, st));
     OVL_HIP(launch_norm2(L, b, partials, st));
@@ -248,8 +251,8 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
     B.shift = s0;
     B.alpha = S->alpha;
     const int npart = stencil_partials(L, P_F64, R);
-    const ProArgs pa{PRO_ALPHA, npart, pstr, partials, S, nullptr, 0.0};
-    const ProArgs pb{PRO_BETA, npart, pstr, partials, S, nullptr, 0.0};
+    const ProArgs pa{PRO_ALPHA, npart, pstr, partials, S, nullptr, 0.0, 0};
+    const ProArgs pb{PRO_BETA, npart, pstr, partials, S, nullptr, 0.0, 0};
 
     const int check = prm->check_every > 0 ? prm->check_every : 10;
     int it = 0;
@@ -273,7 +276,7 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
             prof.pair(OVL_K_SCALAR, &v0, &v1);
             launch_k(k_ms_beta, dim3(R), dim3(kBlock), st, v0, v1, pb);
             prof.pair(OVL_K_UPDATE, &v0, &v1);
-            launch_k(k_ms_update<P_F64>, sgrid, dim3(kBlock), st, v0, v1, L.g, L.nb, (const MState *)S,
+            launch_k(k_ms_update<P_F64>, dim3(nblk, R, elem_split(nblk * R, nshift)), dim3(kBlock), st, v0, v1, L.g, L.nb, (const MState *)S,
                      (const void *)r.d, (const float *)nullptr, pfl.d, (float *)nullptr, x.d, (float *)nullptr, R);
             OVL_HIP(hipGetLastError());
             stencils += 2;
