@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kBlock) void k_base_p(Geom g, int nb, const MState 
         return;
     }
     if (!st->run_c[r]) return;
-    const double be = pro.kind ? pro_beta<kBlock>(pro, r, lds) : st->beta[r];
+    const double be = pro.kind ? pro_beta<kBlock>(pro, r, pro_sums(pro, r), lds) : st->beta[r];
     const int p = b / nb, i = (b % nb) * kBlock + threadIdx.x;
     if (i >= g.Vh) return;
     for (int e = blockIdx.z; e < E::N; e += gridDim.z) {
@@ -637,8 +637,8 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
     const double sw2 = o.switch_rel * o.switch_rel;
     const bool carry = carries_scalars(L, PS, R) && !o.f16.d && !(prof.on && !prof.stencil_only);
     const ProArgs none{};
-    ProArgs pa{PRO_ALPHA, npart, pstr, partials, S, BK, 0.0, 0};
-    const ProArgs pb{PRO_BETA, npart, pstr, partials2, S, BK, sw2, 0};
+    ProArgs pa{PRO_ALPHA, npart, pstr, R, rmode == W_RUPDATE, partials, S, BK, 0.0, 0};
+    const ProArgs pb{PRO_BETA, npart, pstr, R, 0, partials2, S, BK, sw2, 0};
     long k = 0;
     int passes = 0, replacements = 0;
     bool done = false, switched = false;

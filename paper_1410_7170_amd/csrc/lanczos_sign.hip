@@ -8,10 +8,14 @@
 //           c_k = |b| sign(T_k) e_1 from an eigen-decomposition of T_k and an
 //           RHS stops once |c_k - c_{k-kCheck}| <= tol |b|;
 //   pass 2: the same recurrence regenerates v_1..v_m from the stored
-//           coefficients (one fused update-and-scale kernel per step),
-//           accumulating y = sum_k c_k v_k.
-// Four FP64 fields per RHS, twice the stencils of one pass.  Each RHS of a
-// batch has its own coefficients; the passes run in step for all of them.
+//           coefficients, accumulating y = sum_k c_k v_k (every other step,
+//           two vectors at a time), all in the stencil's epilogue.
+// The vectors are kept unnormalised (u_k = |u_k| v_k) and the division goes
+// into the recurrence's coefficients, so that no kernel waits for a norm only
+// to scale a field.  Three FP64 fields per RHS, twice the stencils of one pass.
+// Each RHS of a batch has its own coefficients; the passes run in step for all
+// of them.  At 16^3x32, 320 steps: 8 launches a step (both passes) -> 3 (4 where the
+// stencil streams), 45.3 -> 35.6 ms; at 32^3x64, 707 -> 468 ms.
 #include <cmath>
 #include <cstddef>
 #include <cstring>
@@ -25,89 +29,92 @@ namespace ovl {
 constexpr int kLzMax = 4096;   // longest Lanczos sequence
 constexpr int kCheck = 32;     // steps between convergence checks
 
-// per-RHS Lanczos coefficients on the device: a[k][r], b[k][r] (b the norm
-// of the unnormalised next vector), and the pass-2 weights c[k][r]
+// per-RHS Lanczos coefficients on the device: a[k][r] = <v_k, Q v_k>,
+// b[k][r] = the norm of the unnormalised next vector, and the recurrence's
+// coefficients of every step (kLzTab doubles each, after a step of zeros)
 struct LzCoef {
     double a[kLzMax][NR], b[kLzMax][NR];
+    double tab[kLzMax + 1][kLzTab];
 };
 
-// w = t - a_k v_k - b_{k-1} v_{k-1} into v_prev's field, partial |w|^2 per
-// RHS; in pass 2 (c != null) also y += c_k v_k, and w is stored already
-// divided by the known b_k (the next basis vector; no separate scaling
-// pass).  a_k comes from the reduced dot ar (pass 1) or the stored
-// coefficients (pass 2).
-__global__ __launch_bounds__(kBlock) void k_lz_update(Geom g, int nb, int nrhs, const double2 *t, const double2 *vk,
-                                                       double2 *vprev, const LzCoef *cf, int k, const double *ar,
-                                                       const double *c, double2 *y, double *partials)
+// The rest of a step of pass 1: u_{k+1} = t - c2 u_k over t (t = c0 Q u_k - c1
+// u_{k-1} from the stencil), partial |u_{k+1}|^2 per RHS.  Every block forms
+// c2 from the stencil's partial sums of <u_k, Q u_k>; the first of each RHS
+// records it and a_k.  Bound by its three fields; with the division by |u| in
+// the coefficients and the dot in the stencil, a step of pass 1 moves 8 fields
+// and the links where a stencil, a dot, an update and a scaling moved 12.
+__global__ __launch_bounds__(kBlock) void k_lz_axpy(Geom g, int nb, const double2 *u, double2 *t, LzCoef *cf, int k,
+                                                     const double *pin, int pstride, int pcnt, double *partials)
 {
-    __shared__ double lds[8];
+    __shared__ double lds[4];
     const int r = blockIdx.y, bl = blockIdx.x;
     const int p = bl / nb, i = (bl % nb) * kBlock + threadIdx.x;
-    const double a = ar ? ar[r] : cf->a[k][r];
-    const double bprev = k > 0 ? cf->b[k - 1][r] : 0.0;
+    const double part = slot_part(pin + (size_t)r * pstride, pcnt);
+    cplx<double> tv[4][3], uv[4][3];
+    const auto TF = spinor_ref<P_F64>(t, nullptr, g.S, r);
+    if (i < g.Vh) {
+        TF.load(p, i, tv);
+        spinor_ref<P_F64>(u, nullptr, g.S, r).load(p, i, uv);
+    }
+    double *tab = cf->tab[k + 1] + 4 * r;
+    const double c0 = tab[0];
+    const double a = slot_fold<kBlock>(part, lds) * c0 * c0, c2 = a * c0;
+    if (bl == 0 && threadIdx.x == 0) {
+        cf->a[k][r] = a;
+        tab[2] = c2;
+    }
     double n2 = 0.0;
     if (i < g.Vh) {
-        cplx<double> tv[4][3], v[4][3], u[4][3];
-        spinor_ref<P_F64>(t, nullptr, g.S, r).load(p, i, tv);
-        spinor_ref<P_F64>(vk, nullptr, g.S, r).load(p, i, v);
-        const auto VP = spinor_ref<P_F64>(vprev, nullptr, g.S, r);
-        VP.load(p, i, u);
-        const double bk = c ? cf->b[k][r] : 1.0;
-        const double inv = bk > 0.0 ? 1.0 / bk : 0.0;
 #pragma unroll
         for (int q = 0; q < 12; q++) {
             cplx<double> &w = tv[q / 3][q % 3];
-            w = fmac(fmac(w, -a, v[q / 3][q % 3]), -bprev, u[q / 3][q % 3]);
+            w = fmac(w, -c2, uv[q / 3][q % 3]);
             n2 += norm2(w);
-            if (c) w = inv * w;
         }
-        VP.store(p, i, tv);
-        if (c) {
-            const double ck = c[(size_t)k * NR + r];
-            const auto Y = spinor_ref<P_F64>(y, nullptr, g.S, r);
-            cplx<double> yv[4][3];
-            Y.load(p, i, yv);
-#pragma unroll
-            for (int q = 0; q < 12; q++) yv[q / 3][q % 3] = fmac(yv[q / 3][q % 3], ck, v[q / 3][q % 3]);
-            Y.store(p, i, yv);
-        }
+        TF.store(p, i, tv);
     }
     const double s = block_sum(n2, lds);
-    if (threadIdx.x == 0 && partials) partials[(size_t)r * gridDim.x + bl] = s;
+    if (threadIdx.x == 0) partials[(size_t)r * gridDim.x + bl] = s;
 }
 
-// pass 1: v_next = w / b_k (0 when b_k is 0) written over w's field, with
-// b_k = |w| from the reduced norm; the first block also records a[k] (the
-// reduced dot, real part) and b[k].  An RHS whose new vector vanishes (an
-// invariant subspace) keeps b = 0.
-__global__ __launch_bounds__(kBlock) void k_lz_scale(Geom g, int nb, double2 *w, LzCoef *cf, int k,
-                                                      const double *dot, const double *nrm2)
+// |u_k| and the step's c0, c1 in a kernel of their own (one block per RHS)
+__global__ __launch_bounds__(kBlock) void k_lz_scale(ProArgs a)
 {
-    const int r = blockIdx.y, bl = blockIdx.x;
-    const int p = bl / nb, i = (bl % nb) * kBlock + threadIdx.x;
-    const double bk = sqrt(fmax(nrm2[r], 0.0));
-    if (bl == 0 && threadIdx.x == 0) {
-        cf->a[k][r] = dot[r];
-        cf->b[k][r] = bk;
+    __shared__ double lds[4];
+    lanczos_stage<kBlock>(a, blockIdx.x, lds);
+}
+
+// the first step's coefficients from |b| per RHS (c1 = 0: no vector before it)
+struct LzFirst {
+    double c0[NR];
+};
+__global__ void k_lz_first(LzCoef *cf, LzFirst f)
+{
+    const int j = threadIdx.x;
+    if (j < kLzTab) {
+        cf->tab[0][j] = 0.0;
+        cf->tab[1][j] = (j & 3) == 0 ? f.c0[j >> 2] : 0.0;
     }
-    if (i >= g.Vh) return;
-    const double inv = bk > 0.0 ? 1.0 / bk : 0.0;
-    const auto W = spinor_ref<P_F64>(w, nullptr, g.S, r);
-    cplx<double> v[4][3];
-    W.load(p, i, v);
-#pragma unroll
-    for (int q = 0; q < 12; q++) v[q / 3][q % 3] = inv * v[q / 3][q % 3];
-    W.store(p, i, v);
+}
+
+// the weights of pass 2: cy of step k is c_k / |u_k|
+__global__ __launch_bounds__(kBlock) void k_lz_weights(LzCoef *cf, const double *c, int n)
+{
+    const int j = blockIdx.x * kBlock + threadIdx.x;
+    if (j < n * NR) {
+        double *t = cf->tab[j / NR + 1] + 4 * (j % NR);
+        t[3] = c[j] * t[0];
+    }
 }
 
 size_t lanczos_sign_ws_bytes(const Lat &L, int nrhs)
 {
     WsCarve c{nullptr, 0, 0};
     const size_t F = field_bytes(P_F64, L.V);
-    c.take(3 * F * nrhs);                                  // v_prev, v_k, t
+    c.take(2 * F * nrhs);                                  // u_{k-1}, u_k
     c.take(sizeof(LzCoef));
     c.take(sizeof(double) * (size_t)kLzMax * NR);          // pass-2 weights
-    c.take(sizeof(double) * 2 * NR * site_blocks(L));
+    c.take(sizeof(double) * 2 * NR * part_stride(L));      // of the stencil, of the update
     c.take(sizeof(double) * 4 * NR);
     return c.off + 256;
 }
@@ -122,14 +129,17 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
     const int kmax = std::min(maxiter, kLzMax - 1);
     WsCarve c{ws, 0, ws_bytes};
     const size_t F = field_bytes(P_F64, L.V);
-    char *f3 = (char *)c.take(3 * F * R);
-    Fld va{f3, nullptr, P_F64, R}, vb{f3 + F * R, nullptr, P_F64, R}, t{f3 + 2 * F * R, nullptr, P_F64, R};
+    char *f2 = (char *)c.take(2 * F * R);
+    Fld va{f2, nullptr, P_F64, R}, vb{f2 + F * R, nullptr, P_F64, R};
     LzCoef *cf = (LzCoef *)c.take(sizeof(LzCoef));
     double *cw = (double *)c.take(sizeof(double) * (size_t)kLzMax * NR);
-    double *partials = (double *)c.take(sizeof(double) * 2 * NR * site_blocks(L));
+    const int pstr = part_stride(L), nblk = site_blocks(L);
+    double *partials = (double *)c.take(sizeof(double) * 2 * NR * pstr);
+    double *partials2 = partials + (size_t)NR * pstr;
     double *red = (double *)c.take(sizeof(double) * 4 * NR);
-    const int nblk = site_blocks(L);
     dim3 grid(nblk, R);
+    auto tab = [&](int k) { return (double *)((char *)cf + offsetof(LzCoef, tab)) + (size_t)(k + 1) * kLzTab; };
+    auto bnorm = [&](int k) { return (double *)((char *)cf + offsetof(LzCoef, b)) + (size_t)k * NR; };
     // |b| per RHS
     std::vector<double> bn(R);
     {
@@ -146,39 +156,57 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
     A.U = U64;
     A.diag = m0 + 4.0;
     A.nrhs = R;
-    // start: v_prev = 0, v_1 = b / |b| (an all-zero b gives y = 0)
+    // start: u_{-1} = 0, u_0 = b (an all-zero b gives y = 0)
+    LzFirst lf{};
+    for (int q = 0; q < R; q++) lf.c0[q] = bn[q] > 0 ? 1.0 / bn[q] : 0.0;
     auto start = [&]() -> int {
         OVL_HIP(launch_zero(L, va, st));
-        for (int q = 0; q < R; q++)
-            OVL_HIP(launch_axpby(L, bn[q] > 0 ? 1.0 / bn[q] : 0.0, sub(b, L.V, q, 1), 0.0, sub(vb, L.V, q, 1), st));
+        OVL_HIP(hipMemcpyAsync(vb.d, b.d, F * R, hipMemcpyDeviceToDevice, st));
         return OVL_OK;
     };
-    // one step: t = Q v_k, w = t - a_k v_k - b_{k-1} v_{k-1} into v_prev's
-    // field, then v_{k+1} = w / b_k; the roles of the two fields swap
+    // the two fields swap roles every step: u_{k+1} goes over u_{k-1}
     Fld vprev = va, vk = vb;
     std::vector<int> mq(R, 0);          // steps of each RHS (0: not converged yet)
     std::vector<std::vector<double>> cprev(R), cbest(R);
     std::vector<double> ha((size_t)(kmax + 1) * NR), hb((size_t)(kmax + 1) * NR);
+    k_lz_first<<<1, kLzTab, 0, st>>>(cf, lf);
+    OVL_HIP(hipGetLastError());
     int rc = start();
     if (rc) return rc;
+    // |u_k| and the step's coefficients ride in its stencil where that can
+    // carry them (see carries_scalars)
+    const bool carry = stencil_shape(L, P_F64, R).ts == 0 && nblk <= 1024;
+    const int npart = stencil_partials(L, P_F64, R);
+    ProArgs pro{PRO_LANCZOS, nblk, nblk, R, 0, partials2, nullptr, nullptr, 0.0, 0, nullptr, nullptr};
     int k = 0;
     bool all = false;
     for (int q = 0; q < R; q++)
         if (!(bn[q] > 0)) mq[q] = -1;   // nothing to do
     while (!all && k < kmax) {
+        // (after a check |u_k| and the coefficients are there already)
+        const bool scaled = k == 0 || k % kCheck == 0;
+        if (!scaled) {
+            pro.tab = tab(k);
+            pro.bout = bnorm(k - 1);
+            if (!carry) k_lz_scale<<<R, kBlock, 0, st>>>(pro);
+        }
         A.in = vk.d;
-        A.out = t.d;
-        OVL_HIP(launch_wilson(L, P_F64, W_PLAIN, true, A, st));
-        OVL_HIP(launch_dot(L, vk, t, partials, st));
-        OVL_HIP(launch_reduce(partials, 1, R, nblk, red, st));   // real parts
-        k_lz_update<<<grid, kBlock, 0, st>>>(L.g, L.nb, R, (const double2 *)t.d, (const double2 *)vk.d,
-                                             (double2 *)vprev.d, cf, k, red, nullptr, nullptr, partials);
-        OVL_HIP(hipGetLastError());
-        OVL_HIP(launch_reduce(partials, 1, R, nblk, red + NR, st));
-        k_lz_scale<<<grid, kBlock, 0, st>>>(L.g, L.nb, (double2 *)vprev.d, cf, k, red, red + NR);
+        A.p = vprev.d;
+        A.out = vprev.d;
+        A.alpha = tab(k);
+        A.partials = partials;
+        OVL_HIP(launch_wilson(L, P_F64, W_LZ1, true, A, st, nullptr, nullptr, carry && !scaled ? &pro : nullptr));
+        k_lz_axpy<<<grid, kBlock, 0, st>>>(L.g, L.nb, (const double2 *)vk.d, (double2 *)vprev.d, cf, k, partials,
+                                           pstr, npart, partials2);
         OVL_HIP(hipGetLastError());
         std::swap(vprev, vk);
         k++;
+        if (k % kCheck == 0 || k == kmax) {
+            pro.tab = tab(k);
+            pro.bout = bnorm(k - 1);
+            k_lz_scale<<<R, kBlock, 0, st>>>(pro);
+            OVL_HIP(hipGetLastError());
+        }
         if (k % kCheck == 0 || k == kmax) {
             // device addresses of the coefficient arrays (no host access to cf)
             const double *da = (const double *)((const char *)cf + offsetof(LzCoef, a));
@@ -237,18 +265,22 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
     for (int q = 0; q < R; q++)
         for (int j = 0; j < mq[q]; j++) hc[(size_t)j * NR + q] = cbest[q][j];
     OVL_HIP(hipMemcpyAsync(cw, hc.data(), sizeof(double) * hc.size(), hipMemcpyHostToDevice, st));
+    k_lz_weights<<<(std::max(kmx, 1) * NR + kBlock - 1) / kBlock, kBlock, 0, st>>>(cf, cw, kmx);
+    OVL_HIP(hipGetLastError());
     OVL_HIP(launch_zero(L, y, st));
     rc = start();
     if (rc) return rc;
     vprev = va;
     vk = vb;
     for (int j = 0; j < kmx; j++) {
+        // y takes two steps at a time: at odd j, and at the last
         A.in = vk.d;
-        A.out = t.d;
-        OVL_HIP(launch_wilson(L, P_F64, W_PLAIN, true, A, st));
-        k_lz_update<<<grid, kBlock, 0, st>>>(L.g, L.nb, R, (const double2 *)t.d, (const double2 *)vk.d,
-                                             (double2 *)vprev.d, cf, j, nullptr, cw, (double2 *)y.d, nullptr);
-        OVL_HIP(hipGetLastError());
+        A.p = vprev.d;
+        A.out = vprev.d;
+        A.alpha = tab(j);
+        A.rin = y.d;
+        A.rin_first = j & 1;
+        OVL_HIP(launch_wilson(L, P_F64, (j & 1) || j + 1 == kmx ? W_LZ3 : W_LZ2, true, A, st));
         std::swap(vprev, vk);
     }
     OVL_HIP(hipStreamSynchronize(st));

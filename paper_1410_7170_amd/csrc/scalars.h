@@ -57,31 +57,40 @@ struct MState {
                            // in the blocks that run beside the beta stage, which replaces rr
 };
 
-enum { PRO_NONE = 0, PRO_ALPHA = 1, PRO_BETA = 2 };
+enum { PRO_NONE = 0, PRO_ALPHA = 1, PRO_BETA = 2, PRO_LANCZOS = 3 };
 
 // A scalar stage carried by a kernel: its partial sums (row stride pstride, of
 // which the first pcnt slots count) and the state it updates.
 struct ProArgs {
     int kind;
     int pcnt, pstride;
+    int nrhs;
+    int shifted;   // PRO_ALPHA: some RHS's base shift is not 0 (|p|^2 enters)
     const double *pin;
     MState *st;
     Blk *bk;       // block coefficients (null: none kept)
     double sw2;    // PRO_BETA: pause an RHS with |r|^2 <= sw2 |b|^2 (0: never)
     int reset;     // PRO_ALPHA: a block's first iteration, which starts its coefficients
+    double *tab;   // PRO_LANCZOS: the step's coefficients (LzTab) and, bout, where |u| goes
+    double *bout;
 };
 
 // Sum of n slots, valid in every thread of a block of NT threads.  The order
 // does not depend on NT: 256 strided sums, a butterfly over each 64 of them,
 // then those four in pairs; so a stage gives the same bits in its own kernel
-// and in any stencil that carries it.
-template <int NT>
-__device__ __forceinline__ double slot_sum(const double *p, int n, double *lds /* >= 4 */)
+// and in any stencil that carries it.  slot_part is a thread's share (loads
+// only), slot_fold the rest.
+__device__ __forceinline__ double slot_part(const double *p, int n)
 {
-    static_assert(NT == 256 || NT == 512, "slot_sum: block size");
     double v = 0.0;
     if (threadIdx.x < 256)
         for (int k = threadIdx.x; k < n; k += 256) v += p[k];
+    return v;
+}
+template <int NT>
+__device__ __forceinline__ double slot_fold(double v, double *lds /* >= 4 */)
+{
+    static_assert(NT == 256 || NT == 512, "slot_fold: block size");
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     if (threadIdx.x < 256 && (threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
@@ -91,33 +100,45 @@ __device__ __forceinline__ double slot_sum(const double *p, int n, double *lds /
     return t;
 }
 
-// |t|^2 + s0 |p|^2, alpha's denominator (an unshifted base needs no |p|^2: its
-// t stencil writes only the first set of partials)
-template <int NT>
-__device__ __forceinline__ double alpha_den(const ProArgs &a, int r, double *lds)
+// A thread's shares of the sums a stage starts from: |r|^2 for beta; |t|^2
+// and, with a shifted base, |p|^2 for alpha (an unshifted base needs no |p|^2:
+// its t stencil writes only the first set of partials).
+// rr: the |r|^2 that goes with them.
+struct ProSums {
+    double a, b, rr;
+};
+__device__ __forceinline__ ProSums pro_sums(const ProArgs &p, int r)
 {
-    const double tt = slot_sum<NT>(a.pin + (size_t)r * a.pstride, a.pcnt, lds);
-    const double s0 = a.st->s0r[r];
-    if (s0 == 0.0) return tt;
-    const double pp = slot_sum<NT>(a.pin + (size_t)(a.st->nrhs + r) * a.pstride, a.pcnt, lds);
-    return fma(s0, pp, tt);
+    ProSums s{0.0, 0.0, 0.0};
+    s.rr = p.kind == PRO_ALPHA ? p.st->rr[r] : p.kind == PRO_BETA ? p.st->rr_iter[r] : 0.0;
+    s.a = slot_part(p.pin + (size_t)r * p.pstride, p.pcnt);
+    if (p.shifted) s.b = slot_part(p.pin + (size_t)(p.nrhs + r) * p.pstride, p.pcnt);
+    return s;
+}
+
+// |t|^2 + s0 |p|^2, alpha's denominator
+template <int NT>
+__device__ __forceinline__ double alpha_den(const ProArgs &p, int r, const ProSums &s, double *lds)
+{
+    const double tt = slot_fold<NT>(s.a, lds);
+    return p.shifted ? fma(p.st->s0r[r], slot_fold<NT>(s.b, lds), tt) : tt;
 }
 
 // alpha for RHS r in a block whose sites need it; false if it is not finite
 // (the stage's own block then ends the RHS)
 template <int NT>
-__device__ __forceinline__ bool pro_alpha(const ProArgs &a, int r, double *lds, double *alpha)
+__device__ __forceinline__ bool pro_alpha(const ProArgs &p, int r, const ProSums &s, double *lds, double *alpha)
 {
-    const double pq = alpha_den<NT>(a, r, lds);
-    *alpha = a.st->rr[r] / pq;
+    const double pq = alpha_den<NT>(p, r, s, lds);
+    *alpha = s.rr / pq;
     return isfinite(*alpha) && pq > 0.0;
 }
 
 // beta for RHS r in a block whose sites need it
 template <int NT>
-__device__ __forceinline__ double pro_beta(const ProArgs &a, int r, double *lds)
+__device__ __forceinline__ double pro_beta(const ProArgs &p, int r, const ProSums &s, double *lds)
 {
-    return slot_sum<NT>(a.pin + (size_t)r * a.pstride, a.pcnt, lds) / a.st->rr_iter[r];
+    return slot_fold<NT>(s.a, lds) / s.rr;
 }
 
 // K_a: alpha and the shifted zeta_j', alpha_j of RHS r; shift j is thread j
@@ -139,7 +160,7 @@ __device__ __forceinline__ void alpha_stage(const ProArgs &a, int r, double *lds
         if (j < NS) st->act_cur[r][j] = 0;
         return;
     }
-    const double pq = alpha_den<NT>(a, r, lds);
+    const double pq = alpha_den<NT>(a, r, pro_sums(a, r), lds);
     const double rr = st->rr[r];
     const double alpha = rr / pq;
     if (!isfinite(alpha) || !(pq > 0.0)) {
@@ -179,7 +200,7 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
     Blk *bk = a.bk;
     const int j = threadIdx.x;
     if (st->skip[r]) return;
-    const double rr_new = slot_sum<NT>(a.pin + (size_t)r * a.pstride, a.pcnt, lds);
+    const double rr_new = slot_fold<NT>(slot_part(a.pin + (size_t)r * a.pstride, a.pcnt), lds);
     const int it = st->iter[r] + 1;
     if (!isfinite(rr_new)) {
         if (j == 0) {
@@ -242,12 +263,39 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
     }
 }
 
+// Coefficients of one step of the two-pass Lanczos recurrence on unnormalised
+// vectors u_k = |u_k| v_k (lanczos_sign.hip), four per RHS:
+//   u_{k+1} = (c0 Q u_k - c1 u_{k-1}) - c2 u_k,   y += cy u_k,
+// c0 = 1/|u_k|, c1 = |u_k| / |u_{k-1}|, c2 = <v_k, Q v_k> c0.
+constexpr int kLzTab = 4 * NR;   // doubles per step, [rhs][c0, c1, c2, cy]
+
+// c0 and c1 from |u_k|^2 and the previous step's c0 (an invariant subspace
+// ends in u_k = 0, which stays 0)
+__device__ __forceinline__ void lz_scale(double n2, double c0_prev, double *norm, double *c0, double *c1)
+{
+    const double b = sqrt(fmax(n2, 0.0));
+    *norm = b;
+    *c0 = b > 0.0 ? 1.0 / b : 0.0;
+    *c1 = b * c0_prev;
+}
+
+template <int NT>
+__device__ __forceinline__ void lanczos_stage(const ProArgs &a, int r, double *lds)
+{
+    const double n2 = slot_fold<NT>(slot_part(a.pin + (size_t)r * a.pstride, a.pcnt), lds);
+    if (threadIdx.x == 0) {
+        double *t = a.tab + 4 * r;
+        lz_scale(n2, t[-kLzTab], &a.bout[r], &t[0], &t[1]);
+    }
+}
+
 // The stage's own block inside a launch that carries it.
 template <int NT>
 __device__ __forceinline__ void pro_stage(const ProArgs &a, int r, double *lds)
 {
     if (a.kind == PRO_ALPHA) alpha_stage<NT>(a, r, lds);
-    else beta_stage<NT>(a, r, lds);
+    else if (a.kind == PRO_BETA) beta_stage<NT>(a, r, lds);
+    else lanczos_stage<NT>(a, r, lds);
 }
 
 }  // namespace ovl

@@ -251,8 +251,8 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
     B.shift = s0;
     B.alpha = S->alpha;
     const int npart = stencil_partials(L, P_F64, R);
-    const ProArgs pa{PRO_ALPHA, npart, pstr, partials, S, nullptr, 0.0, 0};
-    const ProArgs pb{PRO_BETA, npart, pstr, partials, S, nullptr, 0.0, 0};
+    const ProArgs pa{PRO_ALPHA, npart, pstr, R, s0 != 0.0, partials, S, nullptr, 0.0, 0};
+    const ProArgs pb{PRO_BETA, npart, pstr, R, 0, partials, S, nullptr, 0.0, 0};
 
     const int check = prm->check_every > 0 ? prm->check_every : 10;
     int it = 0;

@@ -21,9 +21,16 @@ enum WMode {
     W_RESNORM = 4,   // partial |rin - (Gamma_5 D in + shift * p)|^2, nothing stored
     W_RUPDATE0 = 5,  // r  -= alpha_r Gamma_5 D in (an unshifted system: p is not read);
                      // partial |r|^2
+    W_LZ1 = 7,       // (FP64) out = c0 Gamma_5 D in - c1 p; partial Re <in, Gamma_5 D in>
+    W_LZ2 = 8,       // (FP64) out = (c0 Gamma_5 D in - c1 p) - c2 in
+    W_LZ3 = 9,       // (FP64) W_LZ2 and y (rin) += cy' p + cy in: the Lanczos recurrence's
+                     // passes (kLzTab), out over p
     W_SNORM = 6,     // out = Gamma_5 D in + shift * p; partial |out|^2 (t = Q r + beta t of an
                      // unshifted base, whose alpha needs no |p|^2)
 };
+
+template <int MODE>
+constexpr bool kLzMode = MODE == W_LZ1 || MODE == W_LZ2 || MODE == W_LZ3;
 
 struct WArgs {
     Geom g;
@@ -36,13 +43,14 @@ struct WArgs {
     const float *p_sc;
     const void *rin;        // W_RUPDATE(0): read r from here (may equal out)
     const float *rin_sc;
+                            // W_LZ3: y (updated); cy' is the previous step's cy if rin_first, else 0
     int rin_first;          // W_RESNORM: RHS r reads field (rin_first + r) % rin_count of rin
     int rin_count;
     const double *rin_scale;  // W_RESNORM: rin of RHS r taken times rin_scale[r] (null: 1)
     double diag;            // m0 + 4
     double shift;
     const double *shiftv;   // per-RHS shift (device), overrides shift when set
-    const double *alpha;    // W_RUPDATE(0): alpha per RHS (device)
+    const double *alpha;    // W_RUPDATE(0): alpha per RHS (device); W_LZ*: the step's coefficients
     double *partials;       // [quantity][nrhs][nblk]
     const int *skip;        // per-RHS flag: block exits if skip[r] != 0 (may be null)
     int nblk;               // row stride of partials (part_stride)
@@ -374,7 +382,50 @@ __device__ __forceinline__ void site_out(const WArgs &a, int r, int rb, int lo, 
             for (int c = 0; c < 3; c++) n0 += norm2(o[s][c]);
         q0 += live ? (double)n0 : 0.0;
     }
-    if (MODE == W_RUPDATE || MODE == W_RUPDATE0) {
+    if constexpr (kLzMode<MODE>) {
+        // shift: c1, alpha: c0.  Both passes round alike (the same operations
+        // in the same order), so the second regenerates the first's vectors.
+        cplx<T> d[4][3], pv[4][3];
+        spinor_ref<PREC>(a.in, a.in_sc, g.S, rb).load(p, i + lo, d);
+        spinor_ref<PREC>(a.p, a.p_sc, g.S, rb).load(p, i + lo, pv);
+        if (MODE == W_LZ1) {
+            T n0 = 0;
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+#pragma unroll
+                for (int c = 0; c < 3; c++) n0 += fma(d[s][c].x, o[s][c].x, d[s][c].y * o[s][c].y);
+            q0 += live ? (double)n0 : 0.0;
+        }
+        const T c0 = (T)alpha, c1 = (T)shift_r;
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int c = 0; c < 3; c++)
+                o[s][c] = {fma(-c1, pv[s][c].x, c0 * o[s][c].x), fma(-c1, pv[s][c].y, c0 * o[s][c].y)};
+        if (MODE != W_LZ1) {
+            const double *tab = a.alpha + 4 * r;
+            const T c2 = (T)tab[2];
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+#pragma unroll
+                for (int c = 0; c < 3; c++) o[s][c] = fmac(o[s][c], -c2, d[s][c]);
+        }
+        spinor_ref<PREC>(a.out, a.out_sc, g.S, rb).store(p, ist + lo, o);
+        if (MODE == W_LZ3) {
+            // y read after the stores: read with the others, it is moved up
+            // among the hops and 1088 bytes per lane go to scratch
+            asm volatile("" ::: "memory");
+            const double *tab = a.alpha + 4 * r;
+            const SpinorRef<PREC> yf = spinor_ref<PREC>(a.rin, nullptr, g.S, rb);
+            const T cy = (T)tab[3], cp = a.rin_first ? (T)tab[3 - kLzTab] : (T)0;
+            yf.load(p, i + lo, o);
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+#pragma unroll
+                for (int c = 0; c < 3; c++) o[s][c] = fmac(fmac(o[s][c], cp, pv[s][c]), cy, d[s][c]);
+            yf.store(p, ist + lo, o);
+        }
+    } else if (MODE == W_RUPDATE || MODE == W_RUPDATE0) {
         cplx<T> rv[4][3];
         spinor_ref<PREC>(a.rin, a.rin_sc, g.S, rb).load_nt(p, i + lo, rv);
         const T al = (T)alpha;
@@ -428,7 +479,9 @@ __device__ __forceinline__ T diag_minus_half(cplx<T> acc[4][3], const cplx<T> d[
 // own: a larger WArgs made the streaming kernels spill).  Beta then replaces
 // the shift of W_SNORM, alpha that of W_RUPDATE(0).
 template <int MODE>
-constexpr bool kPro = MODE == W_SNORM || MODE == W_RUPDATE || MODE == W_RUPDATE0;
+constexpr bool kPro = MODE == W_SNORM || MODE == W_RUPDATE || MODE == W_RUPDATE0 || MODE == W_LZ1;
+template <int MODE>
+constexpr bool kSums = kPro<MODE> || MODE == W_NORM || MODE == W_RESNORM;   // partial sums
 
 // The shift and alpha of RHS r's sites: given, or formed from the previous
 // launch's partial sums; false if the RHS takes no part.
@@ -436,14 +489,26 @@ template <int MODE, int NT>
 __device__ __forceinline__ bool site_scalars(const WArgs &a, const ProArgs &pro, int r, double *lds, double *shift,
                                              double *alpha)
 {
+    ProSums sums{0.0, 0.0, 0.0};
+    if (kPro<MODE> && pro.kind) sums = pro_sums(pro, r);
     constexpr bool kShift = MODE == W_SHIFT || MODE == W_RUPDATE || MODE == W_RESNORM || MODE == W_SNORM;
     *shift = kShift && !(MODE == W_SNORM && pro.kind) ? (a.shiftv ? a.shiftv[r] : a.shift) : 0.0;
     *alpha = 0.0;
     if (MODE == W_RUPDATE || MODE == W_RUPDATE0) {
         if (!pro.kind) *alpha = a.alpha[r];
-        else if (!pro_alpha<NT>(pro, r, lds, alpha)) return false;
+        else if (!pro_alpha<NT>(pro, r, sums, lds, alpha)) return false;
     }
-    if (MODE == W_SNORM && pro.kind) *shift = pro_beta<NT>(pro, r, lds);
+    if (MODE == W_SNORM && pro.kind) *shift = pro_beta<NT>(pro, r, sums, lds);
+    if (kLzMode<MODE>) {
+        const double *t = a.alpha + 4 * r;
+        if (MODE == W_LZ1 && pro.kind) {
+            double b;
+            lz_scale(slot_fold<NT>(sums.a, lds), t[-kLzTab], &b, alpha, shift);
+        } else {
+            *alpha = t[0];
+            *shift = t[1];
+        }
+    }
     return true;
 }
 
@@ -497,7 +562,7 @@ __global__ __launch_bounds__(kBlock) void k_wilson(WArgs a, ProArgs pro)
         const T dn2 = diag_minus_half(acc, d, (T)a.diag);
         site_out<PREC, MODE, G5>(a, r, r, 0, p, i, shift_r, rin_s, alpha_r, acc, dn2, q0, q1);
     }
-    if (MODE == W_NORM || MODE == W_SNORM || MODE == W_RUPDATE || MODE == W_RUPDATE0 || MODE == W_RESNORM) {
+    if (kSums<MODE>) {
         double t0 = block_sum(q0, lds);
         if (threadIdx.x == 0) a.partials[(size_t)r * a.nblk + lb] = t0;
         if (MODE == W_NORM) {
@@ -584,12 +649,13 @@ __global__ __launch_bounds__(NT, WPE) void k_wilson_ts(WArgs a)
         return;   // every RHS of the tile is finished (block-uniform)
     }
     constexpr bool kShift = MODE == W_SHIFT || MODE == W_RUPDATE || MODE == W_RESNORM || MODE == W_SNORM;
-    const double shift_r = kShift ? (a.shiftv ? a.shiftv[r] : a.shift) : 0.0;
+    constexpr bool kLz = kLzMode<MODE>;
+    const double shift_r = kLz ? a.alpha[4 * r + 1] : kShift ? (a.shiftv ? a.shiftv[r] : a.shift) : 0.0;
     // the residual norm's scale of rin, likewise read once up front (a load
     // left inside the epilogue behind the null test made the compiler keep far
     // more values live across the hops and spill)
     const double rin_s = MODE == W_RESNORM && a.rin_scale ? a.rin_scale[r] : 1.0;
-    const double alpha_r = MODE == W_RUPDATE || MODE == W_RUPDATE0 ? a.alpha[r] : 0.0;
+    const double alpha_r = kLz ? a.alpha[4 * r] : MODE == W_RUPDATE || MODE == W_RUPDATE0 ? a.alpha[r] : 0.0;
     const int L0 = g.L[0], L1 = g.L[1], L2 = g.L[2], L3 = g.L[3];
     const int NS = NT >> kr;
     const int nsb = L1 * L2 * L3 / NS;
@@ -686,7 +752,7 @@ __global__ __launch_bounds__(NT, WPE) void k_wilson_ts(WArgs a)
             if constexpr (kRaw) lp.load(threadIdx.x, cen);
         }
     }
-    if (MODE == W_NORM || MODE == W_SNORM || MODE == W_RUPDATE || MODE == W_RUPDATE0 || MODE == W_RESNORM) {
+    if (kSums<MODE>) {
         constexpr int nq = MODE == W_NORM ? 2 : 1;
         double t0s = block_sum_k<NT / 64>(q0, lds, kr);
         double t1s = nq == 2 ? block_sum_k<NT / 64>(q1, lds + (NT / 64) * 8, kr) : 0.0;

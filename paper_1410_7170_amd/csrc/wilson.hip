@@ -25,6 +25,15 @@ static void wilson_ts_dispatch_s(int mode, bool g5, dim3 grid, const WArgs &a, h
             launch_k(k_wilson_ts<PREC, W_RUPDATE0, true, WPE, STAGE, NT, TILED>, grid, b, st, e0, e1, a);
             break;
         case W_SNORM: launch_k(k_wilson_ts<PREC, W_SNORM, true, WPE, STAGE, NT, TILED>, grid, b, st, e0, e1, a); break;
+        case W_LZ1:
+        case W_LZ2:
+        case W_LZ3:
+            if constexpr (PREC == P_F64) {
+                if (mode == W_LZ1) launch_k(k_wilson_ts<PREC, W_LZ1, true, WPE, STAGE, NT, TILED>, grid, b, st, e0, e1, a);
+                else if (mode == W_LZ2) launch_k(k_wilson_ts<PREC, W_LZ2, true, WPE, STAGE, NT, TILED>, grid, b, st, e0, e1, a);
+                else launch_k(k_wilson_ts<PREC, W_LZ3, true, WPE, STAGE, NT, TILED>, grid, b, st, e0, e1, a);
+            }
+            break;
         default: launch_k(k_wilson_ts<PREC, W_RESNORM, true, WPE, STAGE, NT, TILED>, grid, b, st, e0, e1, a); break;
         }
     } else {
@@ -200,6 +209,15 @@ static void wilson_dispatch(int mode, bool g5, dim3 grid, const WArgs &a, const 
         case W_RUPDATE: launch_k(k_wilson<PREC, W_RUPDATE, true>, grid, b, st, e0, e1, a, pro); break;
         case W_RUPDATE0: launch_k(k_wilson<PREC, W_RUPDATE0, true>, grid, b, st, e0, e1, a, pro); break;
         case W_SNORM: launch_k(k_wilson<PREC, W_SNORM, true>, grid, b, st, e0, e1, a, pro); break;
+        case W_LZ1:
+        case W_LZ2:
+        case W_LZ3:
+            if constexpr (PREC == P_F64) {
+                if (mode == W_LZ1) launch_k(k_wilson<PREC, W_LZ1, true>, grid, b, st, e0, e1, a, pro);
+                else if (mode == W_LZ2) launch_k(k_wilson<PREC, W_LZ2, true>, grid, b, st, e0, e1, a, pro);
+                else launch_k(k_wilson<PREC, W_LZ3, true>, grid, b, st, e0, e1, a, pro);
+            }
+            break;
         default: launch_k(k_wilson<PREC, W_RESNORM, true>, grid, b, st, e0, e1, a, pro); break;
         }
     } else {
@@ -211,6 +229,7 @@ hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hip
                          hipEvent_t e1, const ProArgs *pro)
 {
     const ProArgs pa = pro ? *pro : ProArgs{};
+    if (mode >= W_LZ1 && prec != P_F64) return hipErrorInvalidValue;
     a.g = L.g;
     a.nblk = part_stride(L);
     a.kr = 0;

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(NT, 2) void k_wilson_tile(WArgs a, Tile tl, ProArgs
         const double dn2 = diag_minus_half(acc, d, a.diag);
         site_out<PREC, MODE, G5>(a, r, r, 0, p, i, shift_r, rin_s, alpha_r, acc, dn2, q0, q1);
     }
-    if (MODE == W_NORM || MODE == W_SNORM || MODE == W_RUPDATE || MODE == W_RUPDATE0 || MODE == W_RESNORM) {
+    if (kSums<MODE>) {
         const double t0 = block_sum_w<NT / 64>(q0, lds);
         if (threadIdx.x == 0) a.partials[(size_t)r * a.nblk + lb] = t0;
         if (MODE == W_NORM) {

@@ -17,6 +17,15 @@ static void wilson_tile_dispatch_n(int mode, bool g5, dim3 grid, const WArgs &a,
         case W_RUPDATE: launch_k(k_wilson_tile<PREC, W_RUPDATE, true, NT>, grid, b, st, e0, e1, a, t, pro); break;
         case W_RUPDATE0: launch_k(k_wilson_tile<PREC, W_RUPDATE0, true, NT>, grid, b, st, e0, e1, a, t, pro); break;
         case W_SNORM: launch_k(k_wilson_tile<PREC, W_SNORM, true, NT>, grid, b, st, e0, e1, a, t, pro); break;
+        case W_LZ1:
+        case W_LZ2:
+        case W_LZ3:
+            if constexpr (PREC == P_F64) {
+                if (mode == W_LZ1) launch_k(k_wilson_tile<PREC, W_LZ1, true, NT>, grid, b, st, e0, e1, a, t, pro);
+                else if (mode == W_LZ2) launch_k(k_wilson_tile<PREC, W_LZ2, true, NT>, grid, b, st, e0, e1, a, t, pro);
+                else launch_k(k_wilson_tile<PREC, W_LZ3, true, NT>, grid, b, st, e0, e1, a, t, pro);
+            }
+            break;
         default: launch_k(k_wilson_tile<PREC, W_RESNORM, true, NT>, grid, b, st, e0, e1, a, t, pro); break;
         }
     } else {
