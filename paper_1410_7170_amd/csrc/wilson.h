@@ -57,6 +57,8 @@ struct WArgs {
     int nrhs;
     int kr;                 // streaming form: K = 2^kr consecutive lanes hold K RHS of one
                             // site (set by launch_wilson)
+    int grp;                // streaming form: RHS tiles whose blocks run side by side (set
+                            // by launch_wilson)
 };
 
 template <int PREC>
@@ -638,8 +640,13 @@ __global__ __launch_bounds__(NT, WPE) void k_wilson_ts(WArgs a)
     const int K = 1 << kr;
     const int ntile = (a.nrhs + K - 1) >> kr;
     const int lbr = xcd_remap(blockIdx.x, gridDim.x);
-    const int rt = lbr % ntile;
-    const int lb = lbr / ntile;
+    // groups of a.grp RHS tiles one after the other; within a group the tiles
+    // of one block of sites are neighbours and share its links in L2
+    const int gb = a.grp * (int)(gridDim.x / ntile);
+    const int gi = lbr / gb, gl = lbr - gi * gb;
+    const int gn = min(a.grp, ntile - gi * a.grp);
+    const int rt = gi * a.grp + gl % gn;
+    const int lb = gl / gn;
     const int rq = rt * K + (threadIdx.x & (K - 1));
     const int r = rq < a.nrhs ? rq : a.nrhs - 1;   // idle lanes walk the tile's last RHS
     const bool live = rq < a.nrhs && !(a.skip && a.skip[rq]);

@@ -225,6 +225,22 @@ static void wilson_dispatch(int mode, bool g5, dim3 grid, const WArgs &a, const 
     }
 }
 
+// RHS tiles in a group of the streaming form: at most three, the groups
+// alike.  An XCD holds 64 to 128 of its blocks at a time; with every RHS of a
+// block of sites side by side these span few x1 planes, and the x1 neighbours
+// miss L2, with one RHS after the other the links do.  D_W, 12 RHS, us with
+// groups of 12 / 1 / 2 / 3 / 4 / 6 / 8 (FP32, 48-bit, FP64):
+//   32^4       1004 / 932 / 919 / 914 / 919 / 916 / 938
+//              1731 / 1665 / 1581 / 1553 / 1593 / 1584 / 1671
+//              2416 / 2161 / 2093 / 2103 / 2126 / 2128 / 2278
+//   24^3x48     590 / 639 / 603 / 590 / 585 / 588 / 586 (FP32)
+// and 4 RHS at 32^3x64 with groups of 4 / 2: 636 / 623, 1099 / 1062, 1451 / 1396.
+static int group_tiles(int ntile)
+{
+    const int groups = (ntile + 2) / 3;
+    return (ntile + groups - 1) / groups;
+}
+
 hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hipStream_t st, hipEvent_t e0,
                          hipEvent_t e1, const ProArgs *pro)
 {
@@ -250,6 +266,7 @@ hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hip
         // faster
         if (sh.blocks_per_tile > a.nblk || pa.kind) return hipErrorInvalidConfiguration;
         a.kr = sh.kr;
+        a.grp = group_tiles(sh.ntile);
         if (prec == P_F48) a.g.Ts64 = sh.ts;   // the kernel reads its length from there
         dim3 grid((unsigned)sh.blocks_per_tile * sh.ntile);
         if (prec == P_F64) wilson_ts_dispatch<P_F64>(mode, g5, grid, sh.nt, a, st, e0, e1);
