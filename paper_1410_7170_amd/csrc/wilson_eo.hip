@@ -37,17 +37,22 @@ struct EoArgs {
     const void *U;
     double cd, ch;      // out = cd d + ch (Gamma_5) H in
     double *partials;   // NORM: |out|^2 per block
-    const int *done;    // exit at once when *done (may be null)
+    const int *done;    // exit at once when *done (EoState::stop; may be null)
     int p;
 };
 
-// Scalar state of one CGLS run, on the device.
+// Scalar state of one CGLS run, on the device.  Where every block of a vector
+// kernel forms the scalars itself (kCarry) the first one records them while
+// others may still read: gamma has a slot for each parity of the iteration,
+// and stop holds the stage that ended the run (2 it + 1: alpha of iteration it,
+// 2 it + 2: its beta), so that a stage only stands still for earlier ones.
 struct EoState {
-    double gamma;     // |M^H s|^2
+    double gamma[2];  // |M^H s|^2
     double alpha, beta;
     double target2;   // stop when |s|^2 <= target2
     double ss;        // |s|^2 of the last iteration
-    int done;
+    int stop;         // != 0: the run has ended
+    int done;         // how: 1 converged, 2 M p = 0 or not finite, 3 not finite
     int iter;
 };
 
@@ -256,12 +261,12 @@ __global__ __launch_bounds__(kBlock) void k_eo_accum(int Vh, int S, const float4
 }
 
 // fixed-order sum of n partials by one block (thread t sums t, t + 256, ...
-// in order, then the block's fixed shuffle order)
+// in order, then the block's fixed shuffle order), valid in every thread
 __device__ __forceinline__ double sum_partials(const double *p, int n, double *lds)
 {
     double v = 0.0;
     for (int k = threadIdx.x; k < n; k += kBlock) v += p[k];
-    return block_sum(v, lds);
+    return block_sum_all(v, lds);
 }
 
 // CGLS start: s = r (already in place), z = M^H s with gamma = |z|^2 from its
@@ -273,89 +278,128 @@ __global__ __launch_bounds__(kBlock) void k_eo_start(EoState *st, const double *
     const double zz = sum_partials(pz, nz, lds);
     const double ss = sum_partials(ps, ns, lds);
     if (threadIdx.x == 0) {
-        st->gamma = zz;
+        st->gamma[0] = zz;
         st->ss = ss;
         st->target2 = delta * delta * ss;
         st->iter = 0;
         st->alpha = st->beta = 0.0;
         st->done = !(zz > 0.0) || !(ss > st->target2);
+        st->stop = -st->done;   // before every stage
     }
 }
 
-// alpha = gamma / |q|^2
-__global__ __launch_bounds__(kBlock) void k_eo_alpha(EoState *st, const double *pq, int n)
+// The partial sums a vector kernel takes over from the hop before it: up to
+// kCarry (two loads a thread) every block sums them itself, which at 16^3x32
+// saves the two one-block launches of an iteration (solve 9.7 -> 9.1 ms); at
+// 32^3x64 4096 blocks
+// would read 4096 sums each against 6 and 12 us for the launches.
+constexpr int kCarry = 512;
+
+// alpha = gamma / |q|^2, by every block alike; the first records it
+__device__ __forceinline__ double eo_alpha(EoState *st, const double *pq, int n, int it, double *lds, bool first)
 {
-    __shared__ double lds[8];
-    if (st->done) return;
     const double qq = sum_partials(pq, n, lds);
-    if (threadIdx.x == 0) {
-        if (qq > 0.0 && std::isfinite(qq)) {
-            st->alpha = st->gamma / qq;
-        } else {
-            st->alpha = 0.0;
+    const bool ok = qq > 0.0 && std::isfinite(qq);
+    const double al = ok ? st->gamma[it & 1] / qq : 0.0;
+    if (first && threadIdx.x == 0) {
+        st->alpha = al;
+        if (!ok) {
             st->done = 2;
+            st->stop = 2 * it + 1;
         }
     }
-}
-
-// e += alpha p, s -= alpha q (FP32 even halves); partial |s|^2
-__global__ __launch_bounds__(kBlock) void k_eo_update(int Vh, int S, const EoState *st, const float4 *p,
-                                                       const float4 *q, float4 *e, float4 *s, double *partials)
-{
-    __shared__ double lds[8];
-    if (st->done) return;
-    const float al = (float)st->alpha;
-    const int k = blockIdx.x * kBlock + threadIdx.x;
-    double n = 0.0;
-    if (k < 6 * Vh) {
-        const size_t x = even_elem(k, Vh, S);
-        const float4 pv = p[x], qv = q[x];
-        float4 ev = e[x], sv = s[x];
-        ev.x = fmaf(al, pv.x, ev.x); ev.y = fmaf(al, pv.y, ev.y);
-        ev.z = fmaf(al, pv.z, ev.z); ev.w = fmaf(al, pv.w, ev.w);
-        sv.x = fmaf(-al, qv.x, sv.x); sv.y = fmaf(-al, qv.y, sv.y);
-        sv.z = fmaf(-al, qv.z, sv.z); sv.w = fmaf(-al, qv.w, sv.w);
-        e[x] = ev;
-        s[x] = sv;
-        n = sq(sv);
-    }
-    flat_partial(n, partials, lds);
+    return al;
 }
 
 // beta = |z|^2 / gamma, gamma = |z|^2; stop on |s|^2 <= target2
-__global__ __launch_bounds__(kBlock) void k_eo_beta(EoState *st, const double *pz, int nz, const double *ps, int ns)
+__device__ __forceinline__ double eo_beta(EoState *st, const double *pz, const double *ps, int n, int it, double *lds,
+                                           bool first)
 {
-    __shared__ double lds[8];
-    if (st->done) return;
-    const double zz = sum_partials(pz, nz, lds);
-    const double ss = sum_partials(ps, ns, lds);
-    if (threadIdx.x == 0) {
-        st->iter += 1;
+    const double zz = sum_partials(pz, n, lds);
+    const double ss = sum_partials(ps, n, lds);
+    const double be = zz / st->gamma[it & 1];
+    if (first && threadIdx.x == 0) {
+        st->iter = it + 1;
         st->ss = ss;
-        if (!std::isfinite(zz) || !std::isfinite(ss)) {
-            st->done = 3;
-        } else if (ss <= st->target2 || !(zz > 0.0)) {
-            st->done = 1;
+        const int done = !std::isfinite(zz) || !std::isfinite(ss) ? 3 : ss <= st->target2 || !(zz > 0.0) ? 1 : 0;
+        if (done) {
+            st->done = done;
+            st->stop = 2 * it + 2;
         } else {
-            st->beta = zz / st->gamma;
-            st->gamma = zz;
+            st->beta = be;
+            st->gamma[(it + 1) & 1] = zz;
         }
     }
+    return be;
 }
 
-// p = z + beta p (FP32 even halves)
-__global__ __launch_bounds__(kBlock) void k_eo_dir(int Vh, int S, const EoState *st, const float4 *z, float4 *p)
+__global__ __launch_bounds__(kBlock) void k_eo_alpha(EoState *st, const double *pq, int n, int it)
 {
-    if (st->done) return;
-    const float be = (float)st->beta;
-    const int k = blockIdx.x * kBlock + threadIdx.x;
-    if (k >= 6 * Vh) return;
-    const size_t x = even_elem(k, Vh, S);
-    const float4 zv = z[x];
-    float4 pv = p[x];
-    pv.x = fmaf(be, pv.x, zv.x); pv.y = fmaf(be, pv.y, zv.y);
-    pv.z = fmaf(be, pv.z, zv.z); pv.w = fmaf(be, pv.w, zv.w);
-    p[x] = pv;
+    __shared__ double lds[8];
+    if (st->stop) return;
+    eo_alpha(st, pq, n, it, lds, true);
+}
+
+__global__ __launch_bounds__(kBlock) void k_eo_beta(EoState *st, const double *pz, const double *ps, int n, int it)
+{
+    __shared__ double lds[8];
+    if (st->stop) return;
+    eo_beta(st, pz, ps, n, it, lds, true);
+}
+
+// s -= alpha q (FP32 even halves), one thread per site; partial |s|^2.  pq:
+// the n partials alpha comes from, or null where k_eo_alpha has formed it.
+// Bound by its three fields.  The update of e waits for k_eo_turn, which reads p
+// anyway; one thread per site leaves a sixth of the partials of one per
+// element, whose sum took 39 of 680 us an iteration at 32^3x64 (the two sums 12
+// us now, this kernel and k_eo_turn 117 -> 109).
+__global__ __launch_bounds__(kBlock) void k_eo_step(int Vh, int S, EoState *st, const double *pq, int n, int it,
+                                                     const float4 *q, float4 *s, double *partials)
+{
+    __shared__ double lds[8];
+    if (st->stop && st->stop < 2 * it + 1) return;
+    const double al_d = pq ? eo_alpha(st, pq, n, it, lds, blockIdx.x == 0) : st->alpha;
+    const float al = (float)al_d;
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    double nn = 0.0;
+    if (i < Vh) {
+#pragma unroll
+        for (int c = 0; c < 6; c++) {
+            const size_t x = (size_t)c * S + i;
+            const float4 qv = q[x];
+            float4 sv = s[x];
+            sv.x = fmaf(-al, qv.x, sv.x); sv.y = fmaf(-al, qv.y, sv.y);
+            sv.z = fmaf(-al, qv.z, sv.z); sv.w = fmaf(-al, qv.w, sv.w);
+            s[x] = sv;
+            nn += sq(sv);
+        }
+    }
+    flat_partial(nn, partials, lds);
+}
+
+// e += alpha p, p = z + beta p (FP32 even halves), one thread per site; pz, ps
+// as pq of k_eo_step.  Bound by its five fields.
+__global__ __launch_bounds__(kBlock) void k_eo_turn(int Vh, int S, EoState *st, const double *pz, const double *ps,
+                                                     int n, int it, const float4 *z, float4 *p, float4 *e)
+{
+    __shared__ double lds[8];
+    if (st->stop && st->stop < 2 * it + 2) return;
+    const double be_d = pz ? eo_beta(st, pz, ps, n, it, lds, blockIdx.x == 0) : st->beta;
+    const float al = (float)st->alpha, be = (float)be_d;
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= Vh) return;
+#pragma unroll
+    for (int c = 0; c < 6; c++) {
+        const size_t x = (size_t)c * S + i;
+        const float4 zv = z[x];
+        float4 pv = p[x], ev = e[x];
+        ev.x = fmaf(al, pv.x, ev.x); ev.y = fmaf(al, pv.y, ev.y);
+        ev.z = fmaf(al, pv.z, ev.z); ev.w = fmaf(al, pv.w, ev.w);
+        pv.x = fmaf(be, pv.x, zv.x); pv.y = fmaf(be, pv.y, zv.y);
+        pv.z = fmaf(be, pv.z, zv.z); pv.w = fmaf(be, pv.w, zv.w);
+        e[x] = ev;
+        p[x] = pv;
+    }
 }
 
 template <int PREC, bool G5H, bool G5O, bool NORM>
@@ -420,7 +464,8 @@ int wilson_solve_eo(const Lat &L, const ovl_gauge *U, double m0, Fld b, Fld x, d
     double *fpart = (double *)cv.take(sizeof(double) * 2 * site_blocks(L));
     double *fred = (double *)cv.take(sizeof(double) * 2);
     const int Vh = L.Vh, S = L.g.S;
-    const int *done = &es->done;
+    const int *done = &es->stop;
+    const bool carry = nh <= kCarry;
     const double ih = 0.5 / A;   // 1 / (2A)
     int rc = OVL_OK;
 
@@ -472,24 +517,23 @@ int wilson_solve_eo(const Lat &L, const ovl_gauge *U, double m0, Fld b, Fld x, d
             OVL_HIP(hipGetLastError());
             k_eo_lin<P_F32><<<nf32, kBlock, 0, st>>>(Vh, S, 1.0, Zf, 0.0, nullptr, Pf, nullptr);
             OVL_HIP(hipGetLastError());
-            int chunk = std::min(4, maxiter - iters[q]);
+            int chunk = std::min(4, maxiter - iters[q]), it = 0;
             for (;;) {
-                for (int k = 0; k < chunk; k++) {
+                for (int k = 0; k < chunk; k++, it++) {
                     // q = M p = A p - (1/2) H_eo [H_oe p / (2A)], the bracket in p's odd half
                     OVL_HIP((eo_hop<P_F32, false, false, false>(L, 1, Pf, nullptr, Pf, U->f32, 0.0, ih, nullptr,
                                                                  done, st)));
                     OVL_HIP((eo_hop<P_F32, false, false, true>(L, 0, Pf, Pf, Qf, U->f32, A, -0.5, p0, done, st)));
-                    k_eo_alpha<<<1, kBlock, 0, st>>>(es, p0, nh);
-                    OVL_HIP(hipGetLastError());
-                    k_eo_update<<<nf32, kBlock, 0, st>>>(Vh, S, es, (const float4 *)Pf, (const float4 *)Qf,
-                                                        (float4 *)Ef, (float4 *)Sf, p1);
+                    if (!carry) k_eo_alpha<<<1, kBlock, 0, st>>>(es, p0, nh, it);
+                    k_eo_step<<<nh, kBlock, 0, st>>>(Vh, S, es, carry ? p0 : nullptr, nh, it, (const float4 *)Qf,
+                                                      (float4 *)Sf, p1);
                     OVL_HIP(hipGetLastError());
                     OVL_HIP((eo_hop<P_F32, true, false, false>(L, 1, Sf, nullptr, Sf, U->f32, 0.0, ih, nullptr,
                                                                 done, st)));
                     OVL_HIP((eo_hop<P_F32, false, true, true>(L, 0, Sf, Sf, Zf, U->f32, A, -0.5, p0, done, st)));
-                    k_eo_beta<<<1, kBlock, 0, st>>>(es, p0, nh, p1, nf32);
-                    OVL_HIP(hipGetLastError());
-                    k_eo_dir<<<nf32, kBlock, 0, st>>>(Vh, S, es, (const float4 *)Zf, (float4 *)Pf);
+                    if (!carry) k_eo_beta<<<1, kBlock, 0, st>>>(es, p0, p1, nh, it);
+                    k_eo_turn<<<nh, kBlock, 0, st>>>(Vh, S, es, carry ? p0 : nullptr, p1, nh, it, (const float4 *)Zf,
+                                                      (float4 *)Pf, (float4 *)Ef);
                     OVL_HIP(hipGetLastError());
                 }
                 EoState h;
