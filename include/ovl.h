@@ -307,6 +307,9 @@ OVL_API int ovl_unpack_spinor(const ovl_lattice *lat, const ovl_spinor *in, void
 /* Canonical complex128 device gauge field ([V][4][3][3]) to the packed layout
  * of precision prec, written to out (ovl_gauge_bytes(lat, prec) bytes). */
 OVL_API int ovl_pack_gauge(const ovl_lattice *lat, const void *canon, int32_t prec, void *out, void *stream);
+/* The same for every packed copy of out that is not NULL (one at least), in
+ * one pass over the canonical field. */
+OVL_API int ovl_pack_gauge_copies(const ovl_lattice *lat, const void *canon, const ovl_gauge *out, void *stream);
 
 /* ---- operators ---------------------------------------------------------- */
 

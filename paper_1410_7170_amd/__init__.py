@@ -125,6 +125,7 @@ _sig = {
     "ovl_pack_spinor": (c_i32, [P(ovl_lattice), c_vp, P(ovl_spinor), c_vp]),
     "ovl_unpack_spinor": (c_i32, [P(ovl_lattice), P(ovl_spinor), c_vp, c_vp]),
     "ovl_pack_gauge": (c_i32, [P(ovl_lattice), c_vp, c_i32, c_vp, c_vp]),
+    "ovl_pack_gauge_copies": (c_i32, [P(ovl_lattice), c_vp, P(ovl_gauge), c_vp]),
     "ovl_wilson_apply": (c_i32, [P(ovl_lattice), P(ovl_gauge), c_dbl, P(ovl_spinor), P(ovl_spinor), c_vp]),
     "ovl_q_apply": (c_i32, [P(ovl_lattice), P(ovl_gauge), c_dbl, P(ovl_spinor), P(ovl_spinor), c_vp]),
     "ovl_q2_apply": (c_i32, [P(ovl_lattice), P(ovl_gauge), c_dbl, c_dbl, P(ovl_spinor), P(ovl_spinor),
@@ -316,12 +317,14 @@ class Gauge:
         self.lat = lat
         self.bufs = {}
         for p in precs:
-            buf = _dev_buffer(lat.gauge_bytes(p), canon.device)
-            _check(_lib.ovl_pack_gauge(lat.ref, c_vp(canon.data_ptr()), p, c_vp(buf.data_ptr()),
-                                       _stream(stream)), "ovl_pack_gauge")
-            self.bufs[p] = buf
+            if p not in (F64, F32, F16S):
+                _check(ERR_INVALID, "ovl_pack_gauge")
+            self.bufs[p] = _dev_buffer(lat.gauge_bytes(p), canon.device)
         ptr = lambda p: c_vp(self.bufs[p].data_ptr()) if p in self.bufs else None
         self.c = ovl_gauge(ptr(F64), ptr(F32), ptr(F16S))
+        if self.bufs:
+            _check(_lib.ovl_pack_gauge_copies(lat.ref, c_vp(canon.data_ptr()), self.ref, _stream(stream)),
+                   "ovl_pack_gauge")
 
     @property
     def ref(self):

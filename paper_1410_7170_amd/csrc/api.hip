@@ -288,7 +288,18 @@ int ovl_pack_gauge(const ovl_lattice *lat, const void *canon, int32_t prec, void
 {
     if (!lat_ok(lat) || !canon || !out || canon == out || prec < 0 || prec > 2) return OVL_ERR_INVALID;
     Lat L = make_lat(lat);
-    OVL_HIP(launch_pack_gauge(L, canon, prec, out, S(stream)));
+    OVL_HIP(launch_pack_gauge(L, canon, prec == P_F64 ? out : nullptr, prec == P_F32 ? out : nullptr,
+                              prec == P_F16S ? out : nullptr, S(stream)));
+    return OVL_OK;
+}
+
+int ovl_pack_gauge_copies(const ovl_lattice *lat, const void *canon, const ovl_gauge *out, void *stream)
+{
+    if (!lat_ok(lat) || !canon || !out || canon == out->f64 || canon == out->f32 || canon == out->f16)
+        return OVL_ERR_INVALID;
+    if (!out->f64 && !out->f32 && !out->f16) return OVL_ERR_INVALID;
+    Lat L = make_lat(lat);
+    OVL_HIP(launch_pack_gauge(L, canon, (void *)out->f64, (void *)out->f32, (void *)out->f16, S(stream)));
     return OVL_OK;
 }
 

@@ -88,7 +88,7 @@ inline void launch_k(F kern, dim3 grid, dim3 block, hipStream_t st, hipEvent_t e
 hipError_t launch_wilson_mfma(const Lat &L, bool g5, const WArgs &a, hipStream_t st);
 hipError_t launch_pack_spinor(const Lat &L, const void *canon, Fld out, hipStream_t st);
 hipError_t launch_unpack_spinor(const Lat &L, Fld in, void *canon, hipStream_t st);
-hipError_t launch_pack_gauge(const Lat &L, const void *canon, int prec, void *out, hipStream_t st);
+hipError_t launch_pack_gauge(const Lat &L, const void *canon, void *f64, void *f32, void *f16, hipStream_t st);
 // per-block partial sums of |f_r|^2 (or Re/Im <a_r, b_r> when b != null)
 hipError_t launch_norm2(const Lat &L, Fld f, double *partials, hipStream_t st);
 hipError_t launch_diff_norm2(const Lat &L, Fld a, Fld b, double *partials, hipStream_t st);

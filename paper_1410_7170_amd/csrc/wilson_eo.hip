@@ -291,8 +291,8 @@ __global__ __launch_bounds__(kBlock) void k_eo_start(EoState *st, const double *
 // The partial sums a vector kernel takes over from the hop before it: up to
 // kCarry (two loads a thread) every block sums them itself, which at 16^3x32
 // saves the two one-block launches of an iteration (solve 9.7 -> 9.1 ms); at
-// 32^3x64 4096 blocks
-// would read 4096 sums each against 6 and 12 us for the launches.
+// 32^3x64 4096 blocks would read 4096 sums each against 6 and 12 us for the
+// launches.
 constexpr int kCarry = 512;
 
 // alpha = gamma / |q|^2, by every block alike; the first records it
