@@ -39,6 +39,9 @@ struct EoArgs {
     double *partials;   // NORM: |out|^2 per block
     const int *done;    // exit at once when *done (EoState::stop; may be null)
     int p;
+    int desc;           // walk the sites downwards: the kernels of an iteration alternate, so
+                        // that each begins with the links and vectors that the last-level
+                        // cache still holds (hops with a norm at 32^3x64 135 -> 125 us)
 };
 
 // Scalar state of one CGLS run, on the device.  Where every block of a vector
@@ -102,7 +105,7 @@ __global__ __launch_bounds__(kBlock) void k_eo_hop(EoArgs a)
     __shared__ double lds[8];
     if (a.done && *a.done) return;
     const Geom &g = a.g;
-    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    const int bu = xcd_remap(blockIdx.x, gridDim.x), b = a.desc ? gridDim.x - 1 - bu : bu;
     const int jl = b * kBlock + threadIdx.x;
     double q = 0.0;
     if (jl < g.Vh) {
@@ -148,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_eo_hop(EoArgs a)
     }
     if (NORM) {
         const double t = block_sum(q, lds);
-        if (threadIdx.x == 0) a.partials[blockIdx.x] = t;
+        if (threadIdx.x == 0) a.partials[a.desc ? gridDim.x - 1 - blockIdx.x : blockIdx.x] = t;
     }
 }
 
@@ -360,7 +363,7 @@ __global__ __launch_bounds__(kBlock) void k_eo_step(int Vh, int S, EoState *st, 
     if (st->stop && st->stop < 2 * it + 1) return;
     const double al_d = pq ? eo_alpha(st, pq, n, it, lds, blockIdx.x == 0) : st->alpha;
     const float al = (float)al_d;
-    const int i = blockIdx.x * kBlock + threadIdx.x;
+    const int i = xcd_remap(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     double nn = 0.0;
     if (i < Vh) {
 #pragma unroll
@@ -386,7 +389,7 @@ __global__ __launch_bounds__(kBlock) void k_eo_turn(int Vh, int S, EoState *st, 
     if (st->stop && st->stop < 2 * it + 2) return;
     const double be_d = pz ? eo_beta(st, pz, ps, n, it, lds, blockIdx.x == 0) : st->beta;
     const float al = (float)st->alpha, be = (float)be_d;
-    const int i = blockIdx.x * kBlock + threadIdx.x;
+    const int i = (gridDim.x - 1 - xcd_remap(blockIdx.x, gridDim.x)) * kBlock + threadIdx.x;
     if (i >= Vh) return;
 #pragma unroll
     for (int c = 0; c < 6; c++) {
@@ -404,9 +407,10 @@ __global__ __launch_bounds__(kBlock) void k_eo_turn(int Vh, int S, EoState *st, 
 
 template <int PREC, bool G5H, bool G5O, bool NORM>
 hipError_t eo_hop(const Lat &L, int p, const void *in, const void *d, void *out, const void *U, double cd, double ch,
-                  double *partials, const int *done, hipStream_t st)
+                  double *partials, const int *done, hipStream_t st, int desc = 0)
 {
     EoArgs a{};
+    a.desc = desc;
     a.g = L.g;
     a.in = in;
     a.d = d;
@@ -523,13 +527,13 @@ int wilson_solve_eo(const Lat &L, const ovl_gauge *U, double m0, Fld b, Fld x, d
                     // q = M p = A p - (1/2) H_eo [H_oe p / (2A)], the bracket in p's odd half
                     OVL_HIP((eo_hop<P_F32, false, false, false>(L, 1, Pf, nullptr, Pf, U->f32, 0.0, ih, nullptr,
                                                                  done, st)));
-                    OVL_HIP((eo_hop<P_F32, false, false, true>(L, 0, Pf, Pf, Qf, U->f32, A, -0.5, p0, done, st)));
+                    OVL_HIP((eo_hop<P_F32, false, false, true>(L, 0, Pf, Pf, Qf, U->f32, A, -0.5, p0, done, st, 1)));
                     if (!carry) k_eo_alpha<<<1, kBlock, 0, st>>>(es, p0, nh, it);
                     k_eo_step<<<nh, kBlock, 0, st>>>(Vh, S, es, carry ? p0 : nullptr, nh, it, (const float4 *)Qf,
                                                       (float4 *)Sf, p1);
                     OVL_HIP(hipGetLastError());
                     OVL_HIP((eo_hop<P_F32, true, false, false>(L, 1, Sf, nullptr, Sf, U->f32, 0.0, ih, nullptr,
-                                                                done, st)));
+                                                                done, st, 1)));
                     OVL_HIP((eo_hop<P_F32, false, true, true>(L, 0, Sf, Sf, Zf, U->f32, A, -0.5, p0, done, st)));
                     if (!carry) k_eo_beta<<<1, kBlock, 0, st>>>(es, p0, p1, nh, it);
                     k_eo_turn<<<nh, kBlock, 0, st>>>(Vh, S, es, carry ? p0 : nullptr, p1, nh, it, (const float4 *)Zf,
