@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kBlock) void k_base_p(Geom g, int nb, const MState 
         return;
     }
     if (!st->run_c[r]) return;
-    const double be = pro.kind ? pro_beta<kBlock>(pro, r, pro_sums(pro, r), lds) : st->beta[r];
+    const double be = pro.kind ? pro_beta<kBlock>(pro, r, pro_sums<kBlock>(pro, r), lds) : st->beta[r];
     const int p = b / nb, i = (b % nb) * kBlock + threadIdx.x;
     if (i >= g.Vh) return;
     for (int e = blockIdx.z; e < E::N; e += gridDim.z) {

@@ -583,9 +583,10 @@ __device__ __forceinline__ double block_sum_w(double v, double *lds /* >= 4 */)
     if constexpr (NW == 4) {
         return block_sum(v, lds);
     } else {
-        static_assert(NW == 3 || NW == 8, "block_sum_w: 3, 4 or 8 waves");
+        static_assert(NW == 1 || NW == 3 || NW == 8, "block_sum_w: 1, 3, 4 or 8 waves");
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if constexpr (NW == 1) return v;
         int w = threadIdx.x >> 6;
         if ((threadIdx.x & 63) == 0) lds[w] = v;
         __syncthreads();

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kBlock) void k_lz_axpy(Geom g, int nb, const double
     __shared__ double lds[4];
     const int r = blockIdx.y, bl = blockIdx.x;
     const int p = bl / nb, i = (bl % nb) * kBlock + threadIdx.x;
-    const double part = slot_part(pin + (size_t)r * pstride, pcnt);
+    const SlotPart<kBlock> part = slot_part<kBlock>(pin + (size_t)r * pstride, pcnt);
     cplx<double> tv[4][3], uv[4][3];
     const auto TF = spinor_ref<P_F64>(t, nullptr, g.S, r);
     if (i < g.Vh) {

@@ -79,21 +79,33 @@ struct ProArgs {
 // does not depend on NT: 256 strided sums, a butterfly over each 64 of them,
 // then those four in pairs; so a stage gives the same bits in its own kernel
 // and in any stencil that carries it.  slot_part is a thread's share (loads
-// only), slot_fold the rest.
-__device__ __forceinline__ double slot_part(const double *p, int n)
+// only; a block of one wave holds four of the strided sums per thread),
+// slot_fold the rest.
+template <int NT>
+struct SlotPart {
+    static constexpr int N = NT == 64 ? 4 : 1;
+    double v[N] = {};
+};
+template <int NT>
+__device__ __forceinline__ SlotPart<NT> slot_part(const double *p, int n)
 {
-    double v = 0.0;
+    SlotPart<NT> s;
     if (threadIdx.x < 256)
-        for (int k = threadIdx.x; k < n; k += 256) v += p[k];
-    return v;
+#pragma unroll
+        for (int w = 0; w < SlotPart<NT>::N; w++)
+            for (int k = threadIdx.x + 64 * w; k < n; k += 256) s.v[w] += p[k];
+    return s;
 }
 template <int NT>
-__device__ __forceinline__ double slot_fold(double v, double *lds /* >= 4 */)
+__device__ __forceinline__ double slot_fold(SlotPart<NT> s, double *lds /* >= 4 */)
 {
-    static_assert(NT == 256 || NT == 512, "slot_fold: block size");
+    static_assert(NT == 64 || NT == 256 || NT == 512, "slot_fold: block size");
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if (threadIdx.x < 256 && (threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    for (int w = 0; w < SlotPart<NT>::N; w++)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s.v[w] += __shfl_xor(s.v[w], off, 64);
+    if constexpr (NT == 64) return (s.v[0] + s.v[1]) + (s.v[2] + s.v[3]);
+    if (threadIdx.x < 256 && (threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s.v[0];
     __syncthreads();
     const double t = (lds[0] + lds[1]) + (lds[2] + lds[3]);
     __syncthreads();
@@ -104,21 +116,24 @@ __device__ __forceinline__ double slot_fold(double v, double *lds /* >= 4 */)
 // and, with a shifted base, |p|^2 for alpha (an unshifted base needs no |p|^2:
 // its t stencil writes only the first set of partials).
 // rr: the |r|^2 that goes with them.
+template <int NT>
 struct ProSums {
-    double a, b, rr;
+    SlotPart<NT> a, b;
+    double rr = 0.0;
 };
-__device__ __forceinline__ ProSums pro_sums(const ProArgs &p, int r)
+template <int NT>
+__device__ __forceinline__ ProSums<NT> pro_sums(const ProArgs &p, int r)
 {
-    ProSums s{0.0, 0.0, 0.0};
+    ProSums<NT> s;
     s.rr = p.kind == PRO_ALPHA ? p.st->rr[r] : p.kind == PRO_BETA ? p.st->rr_iter[r] : 0.0;
-    s.a = slot_part(p.pin + (size_t)r * p.pstride, p.pcnt);
-    if (p.shifted) s.b = slot_part(p.pin + (size_t)(p.nrhs + r) * p.pstride, p.pcnt);
+    s.a = slot_part<NT>(p.pin + (size_t)r * p.pstride, p.pcnt);
+    if (p.shifted) s.b = slot_part<NT>(p.pin + (size_t)(p.nrhs + r) * p.pstride, p.pcnt);
     return s;
 }
 
 // |t|^2 + s0 |p|^2, alpha's denominator
 template <int NT>
-__device__ __forceinline__ double alpha_den(const ProArgs &p, int r, const ProSums &s, double *lds)
+__device__ __forceinline__ double alpha_den(const ProArgs &p, int r, const ProSums<NT> &s, double *lds)
 {
     const double tt = slot_fold<NT>(s.a, lds);
     return p.shifted ? fma(p.st->s0r[r], slot_fold<NT>(s.b, lds), tt) : tt;
@@ -127,7 +142,7 @@ __device__ __forceinline__ double alpha_den(const ProArgs &p, int r, const ProSu
 // alpha for RHS r in a block whose sites need it; false if it is not finite
 // (the stage's own block then ends the RHS)
 template <int NT>
-__device__ __forceinline__ bool pro_alpha(const ProArgs &p, int r, const ProSums &s, double *lds, double *alpha)
+__device__ __forceinline__ bool pro_alpha(const ProArgs &p, int r, const ProSums<NT> &s, double *lds, double *alpha)
 {
     const double pq = alpha_den<NT>(p, r, s, lds);
     *alpha = s.rr / pq;
@@ -136,7 +151,7 @@ __device__ __forceinline__ bool pro_alpha(const ProArgs &p, int r, const ProSums
 
 // beta for RHS r in a block whose sites need it
 template <int NT>
-__device__ __forceinline__ double pro_beta(const ProArgs &p, int r, const ProSums &s, double *lds)
+__device__ __forceinline__ double pro_beta(const ProArgs &p, int r, const ProSums<NT> &s, double *lds)
 {
     return slot_fold<NT>(s.a, lds) / s.rr;
 }
@@ -160,7 +175,7 @@ __device__ __forceinline__ void alpha_stage(const ProArgs &a, int r, double *lds
         if (j < NS) st->act_cur[r][j] = 0;
         return;
     }
-    const double pq = alpha_den<NT>(a, r, pro_sums(a, r), lds);
+    const double pq = alpha_den<NT>(a, r, pro_sums<NT>(a, r), lds);
     const double rr = st->rr[r];
     const double alpha = rr / pq;
     if (!isfinite(alpha) || !(pq > 0.0)) {
@@ -200,7 +215,7 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
     Blk *bk = a.bk;
     const int j = threadIdx.x;
     if (st->skip[r]) return;
-    const double rr_new = slot_fold<NT>(slot_part(a.pin + (size_t)r * a.pstride, a.pcnt), lds);
+    const double rr_new = slot_fold<NT>(slot_part<NT>(a.pin + (size_t)r * a.pstride, a.pcnt), lds);
     const int it = st->iter[r] + 1;
     if (!isfinite(rr_new)) {
         if (j == 0) {
@@ -282,7 +297,7 @@ __device__ __forceinline__ void lz_scale(double n2, double c0_prev, double *norm
 template <int NT>
 __device__ __forceinline__ void lanczos_stage(const ProArgs &a, int r, double *lds)
 {
-    const double n2 = slot_fold<NT>(slot_part(a.pin + (size_t)r * a.pstride, a.pcnt), lds);
+    const double n2 = slot_fold<NT>(slot_part<NT>(a.pin + (size_t)r * a.pstride, a.pcnt), lds);
     if (threadIdx.x == 0) {
         double *t = a.tab + 4 * r;
         lz_scale(n2, t[-kLzTab], &a.bout[r], &t[0], &t[1]);

@@ -491,8 +491,8 @@ template <int MODE, int NT>
 __device__ __forceinline__ bool site_scalars(const WArgs &a, const ProArgs &pro, int r, double *lds, double *shift,
                                              double *alpha)
 {
-    ProSums sums{0.0, 0.0, 0.0};
-    if (kPro<MODE> && pro.kind) sums = pro_sums(pro, r);
+    ProSums<NT> sums;
+    if (kPro<MODE> && pro.kind) sums = pro_sums<NT>(pro, r);
     constexpr bool kShift = MODE == W_SHIFT || MODE == W_RUPDATE || MODE == W_RESNORM || MODE == W_SNORM;
     *shift = kShift && !(MODE == W_SNORM && pro.kind) ? (a.shiftv ? a.shiftv[r] : a.shift) : 0.0;
     *alpha = 0.0;
@@ -514,8 +514,8 @@ __device__ __forceinline__ bool site_scalars(const WArgs &a, const ProArgs &pro,
     return true;
 }
 
-template <int PREC, int MODE, bool G5>
-__global__ __launch_bounds__(kBlock) void k_wilson(WArgs a, ProArgs pro)
+template <int PREC, int MODE, bool G5, int NT>
+__global__ __launch_bounds__(NT) void k_wilson(WArgs a, ProArgs pro)
 {
     using T = typename Real<PREC>::T;
     __shared__ double lds[8];
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kBlock) void k_wilson(WArgs a, ProArgs pro)
     // With a scalar stage the launch's first nrhs blocks run it (scalars.h).
     const int first = kPro<MODE> && pro.kind ? a.nrhs : 0;
     if (kPro<MODE> && (int)blockIdx.x < first) {
-        pro_stage<kBlock>(pro, blockIdx.x, lds);
+        pro_stage<NT>(pro, blockIdx.x, lds);
         return;
     }
     const int lbr = xcd_remap(blockIdx.x - first, gridDim.x - first);
@@ -534,13 +534,13 @@ __global__ __launch_bounds__(kBlock) void k_wilson(WArgs a, ProArgs pro)
     if (a.skip && a.skip[r]) return;
     // the epilogue's shift and alpha, read (or formed) once up front (uniform scalars)
     double shift_r, alpha_r;
-    if (!site_scalars<MODE, kBlock>(a, pro, r, lds, &shift_r, &alpha_r)) return;
+    if (!site_scalars<MODE, NT>(a, pro, r, lds, &shift_r, &alpha_r)) return;
     // the residual norm's scale of rin, likewise read once up front (a load
     // left inside the epilogue behind the null test made the compiler keep far
     // more values live across the hops and spill)
     const double rin_s = MODE == W_RESNORM && a.rin_scale ? a.rin_scale[r] : 1.0;
     const int p = lb & 1;
-    const int jl = (lb >> 1) * kBlock + threadIdx.x;
+    const int jl = (lb >> 1) * NT + threadIdx.x;
     const Geom &g = a.g;
     const bool valid = jl < g.Vh;
     const SpinorRef<PREC> in = spinor_ref<PREC>(a.in, a.in_sc, g.S, r);
@@ -565,10 +565,10 @@ __global__ __launch_bounds__(kBlock) void k_wilson(WArgs a, ProArgs pro)
         site_out<PREC, MODE, G5>(a, r, r, 0, p, i, shift_r, rin_s, alpha_r, acc, dn2, q0, q1);
     }
     if (kSums<MODE>) {
-        double t0 = block_sum(q0, lds);
+        double t0 = block_sum_w<NT / 64>(q0, lds);
         if (threadIdx.x == 0) a.partials[(size_t)r * a.nblk + lb] = t0;
         if (MODE == W_NORM) {
-            double t1 = block_sum(q1, lds + 4);
+            double t1 = block_sum_w<NT / 64>(q1, lds + 4);
             if (threadIdx.x == 0) a.partials[(size_t)(a.nrhs + r) * a.nblk + lb] = t1;
         }
     }

@@ -1,6 +1,5 @@
-// Launch of the Wilson stencil kernels (wilson.h, wilson_tile.h): blocks of 256
-// sites (192 for the streaming form on some extents, up to 512 for the tile
-// form), ordered (site block, RHS) and spread over the XCDs by the kernel itself.
+// Launch of the Wilson stencil kernels (wilson.h, wilson_tile.h): blocks of 64 or
+// 256 sites (192 or 256 for the streaming form, up to 512 for the tile form), ordered (site block, RHS) and spread over the XCDs by the kernel itself.
 #include <algorithm>
 #include <cmath>
 
@@ -163,12 +162,38 @@ static int tile_count(const Tile &t) { return t.N[0] * t.N[1] * t.N[2] * t.N[3];
 // 48-bit stencils 381 -> 367 us (t update) and 382 -> 353 us (residual
 // update) against one wave at 32 slices; FP64 itself spills at two waves and
 // keeps one)
+// Blocks of the one-site form: one wave each where a launch leaves no partial
+// sums, so that they spread evenly over the CUs (a wave reads 70 to 150 KB
+// through its CU's L1: D_W at 12^3x20 with 4 RHS FP64 26.8 us with four waves a
+// block, 22.5 with one, FP32 13.0 and 10.0; 22x20x22x24 with 2 RHS FP32 39.0 and
+// 38.2).  With partial sums up to kWaveSites sites, whose sums are then at most
+// one slot to each of the 256 strided sums: the 4^3x8 overlap apply 3.87 and
+// 3.52 ms, 12x8x6x16 multishift 4.75 and 4.17, but at 12^3x18, where every wave
+// would add up 486 slots, 5.51 and 5.67 ms.  The two waves per parity of 4^4
+// gain nothing apart (Q^2 12.7 and 12.9 us).
+constexpr int64_t kWaveSites = 64 * 256;
+constexpr int64_t kTwoWaves = 256;
+
+static int site_threads(const Lat &L, bool sums)
+{
+    return L.V <= kTwoWaves || (sums && L.V > kWaveSites) ? kBlock : 64;
+}
+
+static bool mode_sums(int mode)
+{
+    return mode == W_NORM || mode == W_RUPDATE || mode == W_RUPDATE0 || mode == W_RESNORM || mode == W_SNORM ||
+           mode == W_LZ1;
+}
+
+static int blocks_of(const Lat &L, int nt) { return 2 * ((L.Vh + nt - 1) / nt); }
+
 StencilShape stencil_shape(const Lat &L, int prec, int nrhs)
 {
     const int ts = (prec == P_F64 || prec == P_F48) && L.g.Ts64 > 0 ? L.g.Ts64 : L.g.Ts;
     if (ts <= 0 || prec == P_F16S) {
         StencilShape sh{};
         if (prec == P_F64 || prec == P_F48) sh.tile = L.tile;
+        sh.nt = site_threads(L, true);
         return sh;
     }
     StencilShape sh = stencil_shape_ts(L, ts, nrhs);
@@ -180,12 +205,12 @@ StencilShape stencil_shape(const Lat &L, int prec, int nrhs)
 int stencil_partials(const Lat &L, int prec, int nrhs)
 {
     const StencilShape sh = stencil_shape(L, prec, nrhs);
-    return sh.ts > 0 ? sh.blocks_per_tile : sh.tile.nt ? tile_count(sh.tile) : 2 * L.nb;
+    return sh.ts > 0 ? sh.blocks_per_tile : sh.tile.nt ? tile_count(sh.tile) : blocks_of(L, sh.nt);
 }
 
 int part_stride(const Lat &L)
 {
-    return std::max(2 * L.nb, L.tile.nt ? tile_count(L.tile) : 0);
+    return std::max(blocks_of(L, site_threads(L, true)), L.tile.nt ? tile_count(L.tile) : 0);
 }
 
 // Every block of a carrying launch adds up all of the previous one's partial
@@ -196,32 +221,39 @@ bool carries_scalars(const Lat &L, int prec, int nrhs)
     return stencil_shape(L, prec, nrhs).ts == 0 && stencil_partials(L, prec, nrhs) <= 512;
 }
 
+template <int PREC, int MODE, bool G5>
+static void launch_site(dim3 grid, int nt, const WArgs &a, const ProArgs &pro, hipStream_t st, hipEvent_t e0,
+                        hipEvent_t e1)
+{
+    if (nt == kBlock) launch_k(k_wilson<PREC, MODE, G5, kBlock>, grid, dim3(kBlock), st, e0, e1, a, pro);
+    else launch_k(k_wilson<PREC, MODE, G5, 64>, grid, dim3(64), st, e0, e1, a, pro);
+}
+
 template <int PREC>
-static void wilson_dispatch(int mode, bool g5, dim3 grid, const WArgs &a, const ProArgs &pro, hipStream_t st,
+static void wilson_dispatch(int mode, bool g5, dim3 grid, int nt, const WArgs &a, const ProArgs &pro, hipStream_t st,
                             hipEvent_t e0, hipEvent_t e1)
 {
-    const dim3 b(kBlock);
-    if (g5) {
-        switch (mode) {
-        case W_PLAIN: launch_k(k_wilson<PREC, W_PLAIN, true>, grid, b, st, e0, e1, a, pro); break;
-        case W_NORM: launch_k(k_wilson<PREC, W_NORM, true>, grid, b, st, e0, e1, a, pro); break;
-        case W_SHIFT: launch_k(k_wilson<PREC, W_SHIFT, true>, grid, b, st, e0, e1, a, pro); break;
-        case W_RUPDATE: launch_k(k_wilson<PREC, W_RUPDATE, true>, grid, b, st, e0, e1, a, pro); break;
-        case W_RUPDATE0: launch_k(k_wilson<PREC, W_RUPDATE0, true>, grid, b, st, e0, e1, a, pro); break;
-        case W_SNORM: launch_k(k_wilson<PREC, W_SNORM, true>, grid, b, st, e0, e1, a, pro); break;
-        case W_LZ1:
-        case W_LZ2:
-        case W_LZ3:
-            if constexpr (PREC == P_F64) {
-                if (mode == W_LZ1) launch_k(k_wilson<PREC, W_LZ1, true>, grid, b, st, e0, e1, a, pro);
-                else if (mode == W_LZ2) launch_k(k_wilson<PREC, W_LZ2, true>, grid, b, st, e0, e1, a, pro);
-                else launch_k(k_wilson<PREC, W_LZ3, true>, grid, b, st, e0, e1, a, pro);
-            }
-            break;
-        default: launch_k(k_wilson<PREC, W_RESNORM, true>, grid, b, st, e0, e1, a, pro); break;
+    if (!g5) {
+        launch_site<PREC, W_PLAIN, false>(grid, nt, a, pro, st, e0, e1);
+        return;
+    }
+    switch (mode) {
+    case W_PLAIN: launch_site<PREC, W_PLAIN, true>(grid, nt, a, pro, st, e0, e1); break;
+    case W_NORM: launch_site<PREC, W_NORM, true>(grid, nt, a, pro, st, e0, e1); break;
+    case W_SHIFT: launch_site<PREC, W_SHIFT, true>(grid, nt, a, pro, st, e0, e1); break;
+    case W_RUPDATE: launch_site<PREC, W_RUPDATE, true>(grid, nt, a, pro, st, e0, e1); break;
+    case W_RUPDATE0: launch_site<PREC, W_RUPDATE0, true>(grid, nt, a, pro, st, e0, e1); break;
+    case W_SNORM: launch_site<PREC, W_SNORM, true>(grid, nt, a, pro, st, e0, e1); break;
+    case W_LZ1:
+    case W_LZ2:
+    case W_LZ3:
+        if constexpr (PREC == P_F64) {
+            if (mode == W_LZ1) launch_site<PREC, W_LZ1, true>(grid, nt, a, pro, st, e0, e1);
+            else if (mode == W_LZ2) launch_site<PREC, W_LZ2, true>(grid, nt, a, pro, st, e0, e1);
+            else launch_site<PREC, W_LZ3, true>(grid, nt, a, pro, st, e0, e1);
         }
-    } else {
-        launch_k(k_wilson<PREC, W_PLAIN, false>, grid, b, st, e0, e1, a, pro);
+        break;
+    default: launch_site<PREC, W_RESNORM, true>(grid, nt, a, pro, st, e0, e1); break;
     }
 }
 
@@ -279,11 +311,12 @@ hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hip
         dim3 grid((unsigned)tile_count(sh.tile) * a.nrhs + extra);
         return launch_wilson_tile(prec, mode, g5, grid, a, sh.tile, pa, st, e0, e1);
     }
-    dim3 grid(2 * L.nb * a.nrhs + extra);
-    if (prec == P_F64) wilson_dispatch<P_F64>(mode, g5, grid, a, pa, st, e0, e1);
-    else if (prec == P_F48) wilson_dispatch<P_F48>(mode, g5, grid, a, pa, st, e0, e1);
-    else if (prec == P_F32) wilson_dispatch<P_F32>(mode, g5, grid, a, pa, st, e0, e1);
-    else wilson_dispatch<P_F16S>(mode, g5, grid, a, pa, st, e0, e1);
+    const int nt = mode_sums(mode) ? sh.nt : site_threads(L, false);
+    dim3 grid(blocks_of(L, nt) * a.nrhs + extra);
+    if (prec == P_F64) wilson_dispatch<P_F64>(mode, g5, grid, nt, a, pa, st, e0, e1);
+    else if (prec == P_F48) wilson_dispatch<P_F48>(mode, g5, grid, nt, a, pa, st, e0, e1);
+    else if (prec == P_F32) wilson_dispatch<P_F32>(mode, g5, grid, nt, a, pa, st, e0, e1);
+    else wilson_dispatch<P_F16S>(mode, g5, grid, nt, a, pa, st, e0, e1);
     return hipGetLastError();
 }
 

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 M0 = -1.6
 
 
-@pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 1e-5)])
+@pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 1e-6)])
 @pytest.mark.parametrize("nrhs,tile", [(4, 1), (5, 1), (7, 1), (12, 1), (11, 2)])
 def test_rhs_groups_match_oracle(nrhs, tile, prec, tol):
     import paper_1410_7170_amd as ovl
