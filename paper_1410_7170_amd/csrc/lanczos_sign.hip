@@ -15,7 +15,8 @@
 // to scale a field.  Three FP64 fields per RHS, twice the stencils of one pass.
 // Each RHS of a batch has its own coefficients; the passes run in step for all
 // of them.  At 16^3x32, 320 steps: 8 launches a step (both passes) -> 3 (4 where the
-// stencil streams), 45.3 -> 35.6 ms; at 32^3x64, 707 -> 468 ms.
+// stencil streams), 45.3 -> 35.6 ms, and 30.2 with the checks' host work beside
+// the device's next steps; at 32^3x64, 707 -> 463 ms.
 #include <cmath>
 #include <cstddef>
 #include <cstring>
@@ -182,9 +183,9 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
     bool all = false;
     for (int q = 0; q < R; q++)
         if (!(bn[q] > 0)) mq[q] = -1;   // nothing to do
-    while (!all && k < kmax) {
+    auto step = [&]() -> int {
         // (after a check |u_k| and the coefficients are there already)
-        const bool scaled = k == 0 || k % kCheck == 0;
+        const bool scaled = k % kCheck == 0;
         if (!scaled) {
             pro.tab = tab(k);
             pro.bout = bnorm(k - 1);
@@ -201,49 +202,62 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
         OVL_HIP(hipGetLastError());
         std::swap(vprev, vk);
         k++;
-        if (k % kCheck == 0 || k == kmax) {
-            pro.tab = tab(k);
-            pro.bout = bnorm(k - 1);
-            k_lz_scale<<<R, kBlock, 0, st>>>(pro);
-            OVL_HIP(hipGetLastError());
-        }
-        if (k % kCheck == 0 || k == kmax) {
-            // device addresses of the coefficient arrays (no host access to cf)
-            const double *da = (const double *)((const char *)cf + offsetof(LzCoef, a));
-            const double *db = (const double *)((const char *)cf + offsetof(LzCoef, b));
-            OVL_HIP(hipMemcpyAsync(ha.data(), da, sizeof(double) * NR * k, hipMemcpyDeviceToHost, st));
-            OVL_HIP(hipMemcpyAsync(hb.data(), db, sizeof(double) * NR * k, hipMemcpyDeviceToHost, st));
-            OVL_HIP(hipStreamSynchronize(st));
-            all = true;
-            for (int q = 0; q < R; q++) {
-                if (mq[q] != 0) continue;
-                std::vector<double> a(k), bt(k);
-                bool brk = false;
-                int kk = k;
-                for (int j = 0; j < k; j++) {
-                    a[j] = ha[(size_t)j * NR + q];
-                    bt[j] = hb[(size_t)j * NR + q];
-                    if (!std::isfinite(a[j]) || !std::isfinite(bt[j])) return OVL_ERR_NONFINITE;
-                    if (bt[j] <= 1e-14 * std::fabs(a[j]) + 1e-300) {   // invariant subspace: exact
-                        kk = j + 1;
-                        brk = true;
-                        break;
-                    }
+        return OVL_OK;
+    };
+    while (!all && k < kmax) {
+        const int kc = std::min(kmax, (k / kCheck + 1) * kCheck);   // the next check
+        while (k < kc)
+            if ((rc = step())) return rc;
+        pro.tab = tab(k);
+        pro.bout = bnorm(k - 1);
+        k_lz_scale<<<R, kBlock, 0, st>>>(pro);
+        OVL_HIP(hipGetLastError());
+        // device addresses of the coefficient arrays (no host access to cf)
+        const double *da = (const double *)((const char *)cf + offsetof(LzCoef, a));
+        const double *db = (const double *)((const char *)cf + offsetof(LzCoef, b));
+        OVL_HIP(hipMemcpyAsync(ha.data(), da, sizeof(double) * NR * k, hipMemcpyDeviceToHost, st));
+        OVL_HIP(hipMemcpyAsync(hb.data(), db, sizeof(double) * NR * k, hipMemcpyDeviceToHost, st));
+        OVL_HIP(hipStreamSynchronize(st));
+        // The device goes on while the host decomposes T_k, by no more steps
+        // than that takes (at least 15 ns per row squared of each RHS; a step: its
+        // 8 fields and links at 5 TB/s, or 15 us), so that none delays pass 2
+        // where this check is the last.
+        int open = 0;
+        for (int q = 0; q < R; q++) open += mq[q] == 0;
+        const double host = 15e-9 * k * k * open;
+        const double gpu = std::max(15e-6, 2.5e3 * (double)L.V * R / 5e12);
+        const int ahead = std::min(std::min(kCheck - 1, kmax - k), (int)(host / gpu));
+        for (int j = 0; j < ahead; j++)
+            if ((rc = step())) return rc;
+        all = true;
+        for (int q = 0; q < R; q++) {
+            if (mq[q] != 0) continue;
+            std::vector<double> a(kc), bt(kc);
+            bool brk = false;
+            int kk = kc;
+            for (int j = 0; j < kc; j++) {
+                a[j] = ha[(size_t)j * NR + q];
+                bt[j] = hb[(size_t)j * NR + q];
+                if (!std::isfinite(a[j]) || !std::isfinite(bt[j])) return OVL_ERR_NONFINITE;
+                if (bt[j] <= 1e-14 * std::fabs(a[j]) + 1e-300) {   // invariant subspace: exact
+                    kk = j + 1;
+                    brk = true;
+                    break;
                 }
-                std::vector<double> cq;
-                if (!tridiag_sign_e1(kk, a.data(), bt.data(), bn[q], cq)) return OVL_ERR_NONFINITE;
-                double diff = 0.0;
-                for (int j = 0; j < kk; j++) {
-                    const double o = j < (int)cprev[q].size() ? cprev[q][j] : 0.0;
-                    diff += (cq[j] - o) * (cq[j] - o);
-                }
-                if (brk || std::sqrt(diff) <= tol * bn[q]) {
-                    mq[q] = kk;
-                    cbest[q] = cq;
-                } else {
-                    all = false;
-                    cprev[q] = cq;
-                }
+            }
+            std::vector<double> cq;
+            if (!tridiag_sign_e1(kk, a.data(), bt.data(), bn[q], cq)) return OVL_ERR_NONFINITE;
+            double diff = 0.0;
+            for (int j = 0; j < kk; j++) {
+                const double o = j < (int)cprev[q].size() ? cprev[q][j] : 0.0;
+                diff += (cq[j] - o) * (cq[j] - o);
+            }
+            if (brk || std::sqrt(diff) <= tol * bn[q]) {
+                mq[q] = kk;
+                cbest[q] = cq;
+            } else {
+                all = false;
+                cprev[q] = cq;
             }
         }
     }
