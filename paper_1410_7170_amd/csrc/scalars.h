@@ -229,7 +229,11 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
     const double thr = st->tol2r[r] * st->bb[r];
     const int t = bk ? bk->t[r] : 0;
     int live = 0;
-    if (j < st->nshift && st->act_cur[r][j]) {
+    __shared__ double sa[NS], sb[NS];   // aj, bj of the shifts that run (son)
+    __shared__ int son[NS];
+    const int on = j < st->nshift && st->act_cur[r][j];
+    if (j < NS) son[j] = on;
+    if (on) {
         const double z = st->zeta[r][j], zn = st->zeta_new[r][j];
         const double q = zn / z;
         const double bj = beta * q * q;
@@ -239,11 +243,8 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
             const double P = bk->P[r][j];
             bk->XP[r][j] += aj * P;
             bk->P[r][j] = bj * P;
-            for (int i = 1; i <= t; i++) {
-                const double c = bk->C[r][j][i];
-                bk->X[r][j][i] += aj * c;
-                bk->C[r][j][i] = bj * c;
-            }
+            sa[j] = aj;
+            sb[j] = bj;
             bk->C[r][j][t + 1] = zn;
             bk->X[r][j][t + 1] = 0.0;
         }
@@ -263,6 +264,15 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
     // also the barrier between every thread's reads of rr, iter and t and
     // thread 0's writes below
     const int left = __syncthreads_count(live);
+    // the block's earlier coefficients, a thread each (a thread for all of a
+    // shift's is a chain of t loads and stores: 9.6 -> 7.2 us at up to 32 residuals)
+    for (int k = j; k < st->nshift * t; k += NT) {
+        const int q = k / t, i = 1 + k % t;
+        if (!son[q]) continue;
+        const double c = bk->C[r][q][i];
+        bk->X[r][q][i] += sa[q] * c;
+        bk->C[r][q][i] = sb[q] * c;
+    }
     if (j == 0) {
         st->iter[r] = it;
         st->beta[r] = beta;
