@@ -11,7 +11,7 @@ oracle's stored samples of the same apply (tests/golden), for the error line.
 
 Besides the timed steps the line reports: the stencil's bandwidth in each
 precision; the FP64 forms' applies/s (the speedups are against the fastest of
-them, with the plain form's ratio kept as a second key); the timed result's
+them, with the default FP64 parameters' ratio kept as a second key); the timed result's
 error against the FP64 oracle at the sampled sites and its Ginsparg-Wilson
 residual; the 16^3x32 workload (operator bandwidth, overlap applies); the
 batched 24^3x48 point-source workload; and the oracle's own speed on the
@@ -169,7 +169,7 @@ def params_for(ovl, form, tol, profile=False):
         prm = params_for(ovl, form, tol, profile)
         prm.block = int(m)
         return prm
-    if form == "fp64":       # plain FP64: every shifted vector updated every iteration
+    if form == "fp64":       # FP64 with the default parameters (block = 0)
         return ovl.default_params(tol=tol, maxiter=5000, profile=int(profile))
     if form == "fp64_blocked":
         return ovl.default_params(tol=tol, maxiter=5000, profile=int(profile), block=16)

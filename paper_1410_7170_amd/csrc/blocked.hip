@@ -730,7 +730,7 @@ int mscg_blocked_t(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
         OVL_HIP(hipMemcpyAsync(&h, S, sizeof(MState), hipMemcpyDeviceToHost, st));
         OVL_HIP(hipStreamSynchronize(st));
         // an RHS is finished (skip without pause), paused at the hand-over
-        // level (k_blk_beta stops it at the iteration it gets there) or open;
+        // level (k_ms_beta stops it at the iteration it gets there) or open;
         // the hand-over comes once no RHS is open
         done = true;
         bool want = false;

@@ -12,7 +12,7 @@
 //           two vectors at a time), all in the stencil's epilogue.
 // The vectors are kept unnormalised (u_k = |u_k| v_k) and the division goes
 // into the recurrence's coefficients, so that no kernel waits for a norm only
-// to scale a field.  Three FP64 fields per RHS, twice the stencils of one pass.
+// to scale a field.  Two FP64 work fields per RHS, twice the stencils of one pass.
 // Each RHS of a batch has its own coefficients; the passes run in step for all
 // of them.  At 16^3x32, 320 steps: 8 launches a step (both passes) -> 3 (4 where the
 // stencil streams), 45.3 -> 35.6 ms, and 30.2 with the checks' host work beside
