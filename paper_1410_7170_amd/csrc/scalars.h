@@ -39,7 +39,7 @@ struct MState {
     int frozen_at[NR][NS];
     double frozen_rr[NR][NS];   // zeta^2 |r|^2 of a shift at the iteration it froze
     int iter[NR];
-    int skip[NR];          // RHS finished (every shift frozen) or failed
+    int skip[NR];          // RHS finished (every shift frozen) or failed (set by K_b alone during a solve)
     int nonfinite[NR];
     int nrhs, nshift;
     int jlive;             // an RHS is finished once systems jlive.. are frozen (1: system 0 is a base
@@ -51,7 +51,8 @@ struct MState {
     // hand-over level stops (skip set, paused set) until the solve that
     // continues its recurrences clears both
     int paused[NR];
-    int run_c[NR];         // the RHS takes part in this iteration: its p0 update is due (set and cleared by K_a)
+    int run_c[NR];         // the RHS takes part in this iteration: its p0 (or t) update is due (set and
+                           // cleared by K_a alone)
     double one[NR];        // 1 per RHS: the alpha of a residual replacement's update stencil
     double rr_iter[NR];    // |r|^2 at the start of this iteration (set by K_a): what beta divides by
                            // in the blocks that run beside the beta stage, which replaces rr
@@ -156,8 +157,20 @@ __device__ __forceinline__ double pro_beta(const ProArgs &p, int r, const ProSum
     return slot_fold<NT>(s.a, lds) / s.rr;
 }
 
+// Whether RHS r's sites stand still in a launch that carries stage p (kind 0:
+// none; skip: the launch's flags, may be null).  The stage's block runs beside
+// the site blocks, and every wave of a block must come to the same answer (the
+// sums that follow have barriers), so the answer comes from a flag that the
+// stage does not write: alpha writes run_c and leaves skip alone, beta writes
+// skip and leaves run_c alone.
+__device__ __forceinline__ bool sits_out(const ProArgs &p, const int *skip, int r)
+{
+    return p.kind == PRO_BETA ? !p.st->run_c[r] : skip && skip[r];
+}
+
 // K_a: alpha and the shifted zeta_j', alpha_j of RHS r; shift j is thread j
-// (NS <= 64: all in wave 0)
+// (NS <= 64: all in wave 0).  An RHS without a finite alpha is marked and left
+// out of the iteration; K_b then ends it.
 template <int NT>
 __device__ __forceinline__ void alpha_stage(const ProArgs &a, int r, double *lds)
 {
@@ -183,7 +196,6 @@ __device__ __forceinline__ void alpha_stage(const ProArgs &a, int r, double *lds
         if (j == 0) {
             st->run_c[r] = 0;
             st->nonfinite[r] = 1;
-            st->skip[r] = 1;
         }
         return;
     }
@@ -214,7 +226,10 @@ __device__ __forceinline__ void beta_stage(const ProArgs &a, int r, double *lds)
     MState *st = a.st;
     Blk *bk = a.bk;
     const int j = threadIdx.x;
-    if (st->skip[r]) return;
+    if (!st->run_c[r]) {   // finished before, or without a finite alpha
+        if (j == 0 && st->nonfinite[r]) st->skip[r] = 1;
+        return;
+    }
     const double rr_new = slot_fold<NT>(slot_part<NT>(a.pin + (size_t)r * a.pstride, a.pcnt), lds);
     const int it = st->iter[r] + 1;
     if (!isfinite(rr_new)) {

@@ -531,7 +531,7 @@ __global__ __launch_bounds__(NT) void k_wilson(WArgs a, ProArgs pro)
     const int lbr = xcd_remap(blockIdx.x - first, gridDim.x - first);
     const int r = lbr % a.nrhs;
     const int lb = lbr / a.nrhs;
-    if (a.skip && a.skip[r]) return;
+    if (kPro<MODE> ? sits_out(pro, a.skip, r) : a.skip && a.skip[r]) return;
     // the epilogue's shift and alpha, read (or formed) once up front (uniform scalars)
     double shift_r, alpha_r;
     if (!site_scalars<MODE, NT>(a, pro, r, lds, &shift_r, &alpha_r)) return;

@@ -152,7 +152,7 @@ __global__ __launch_bounds__(NT, 2) void k_wilson_tile(WArgs a, Tile tl, ProArgs
     const int lbr = xcd_remap(blockIdx.x - first, gridDim.x - first);
     const int r = lbr % a.nrhs;
     const int lb = lbr / a.nrhs;
-    if (a.skip && a.skip[r]) return;
+    if (kPro<MODE> ? sits_out(pro, a.skip, r) : a.skip && a.skip[r]) return;
     const double rin_s = MODE == W_RESNORM && a.rin_scale ? a.rin_scale[r] : 1.0;
     TileSite t;
     t.l = threadIdx.x;
