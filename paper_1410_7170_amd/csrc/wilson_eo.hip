@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "eo_plan.h"
 #include "mscg.h"
 
 namespace ovl {
@@ -429,8 +430,8 @@ hipError_t eo_hop(const Lat &L, int p, const void *in, const void *d, void *out,
 }
 
 // Blocks of a flat even-half launch over nc component arrays (12 for FP64
-// double2, 6 for FP32 float4 elements); partial-sum buffers hold the FP64 count.
-inline int flat_blocks(const Lat &L, int nc) { return (nc * L.Vh + kBlock - 1) / kBlock; }
+// double2, 6 for FP32 float4 elements).
+inline int flat_blocks(const Lat &L, int nc) { return eo_flat_blocks(L.Vh, nc, kBlock); }
 
 }  // namespace
 
@@ -440,7 +441,7 @@ size_t wilson_solve_eo_ws_bytes(const Lat &L)
     const size_t F64 = field_bytes(P_F64, L.V), F32 = field_bytes(P_F32, L.V);
     c.take(F64 * 2);                                      // c, r
     c.take(F32 * 5);                                      // s, e, p, q, z
-    c.take(sizeof(double) * 2 * flat_blocks(L, 12));      // partials
+    c.take(sizeof(double) * 2 * eo_plan(L.Vh, kBlock).slots);   // partials
     c.take(sizeof(EoState));
     c.take(sizeof(double) * 2 * site_blocks(L));          // full-field norms
     c.take(sizeof(double) * 2);
@@ -464,18 +465,18 @@ int wilson_solve_eo(const Lat &L, const ovl_gauge *U, double m0, Fld b, Fld x, d
     char *C = (char *)cv.take(F64), *R = (char *)cv.take(F64);
     char *Sf = (char *)cv.take(F32), *Ef = (char *)cv.take(F32), *Pf = (char *)cv.take(F32),
          *Qf = (char *)cv.take(F32), *Zf = (char *)cv.take(F32);
-    const int nf64 = flat_blocks(L, 12), nf32 = flat_blocks(L, 6), nh = (L.Vh + kBlock - 1) / kBlock;
-    double *p0 = (double *)cv.take(sizeof(double) * 2 * nf64);
-    double *p1 = p0 + nf64;
+    const int nf64 = flat_blocks(L, 12), nf32 = flat_blocks(L, 6);
+    const EoPlan plan = eo_plan(L.Vh, kBlock);
+    const int nh = plan.nh;
+    double *p0 = (double *)cv.take(sizeof(double) * 2 * plan.slots);
+    double *p1 = p0 + plan.slots;
     EoState *es = (EoState *)cv.take(sizeof(EoState));
     double *fpart = (double *)cv.take(sizeof(double) * 2 * site_blocks(L));
     double *fred = (double *)cv.take(sizeof(double) * 2);
     const int Vh = L.Vh, S = L.g.S;
     const int *done = &es->stop;
     const bool carry = nh <= kCarry;
-    // a small lattice's vector kernels deal a site's elements to three blocks
-    // (12^3x16, 54 blocks otherwise: solve 2.42 -> 2.35 ms)
-    const dim3 gv(nh, nh <= 128 ? 3 : 1);
+    const dim3 gv(nh, plan.parts);
     const int ns = gv.x * gv.y;
     const double ih = 0.5 / A;   // 1 / (2A)
     int rc = OVL_OK;
