@@ -179,7 +179,7 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
     const bool carry = stencil_shape(L, P_F64, R).ts == 0 && nblk <= 1024;
     const int npart = stencil_partials(L, P_F64, R);
     ProArgs pro{PRO_LANCZOS, nblk, nblk, R, 0, partials2, nullptr, nullptr, 0.0, 0, nullptr, nullptr};
-    int k = 0;
+    int k = 0, checked = 0;   // steps launched, and those of the last check
     bool all = false;
     for (int q = 0; q < R; q++)
         if (!(bn[q] > 0)) mq[q] = -1;   // nothing to do
@@ -204,10 +204,13 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
         k++;
         return OVL_OK;
     };
-    while (!all && k < kmax) {
-        const int kc = std::min(kmax, (k / kCheck + 1) * kCheck);   // the next check
+    // The steps run ahead of the checks (below), never past the next one; the
+    // last check is at kmax, also where the steps have come that far already.
+    while (!all && checked < kmax) {
+        const int kc = std::min(kmax, (checked / kCheck + 1) * kCheck);
         while (k < kc)
             if ((rc = step())) return rc;
+        checked = kc;
         pro.tab = tab(k);
         pro.bout = bnorm(k - 1);
         k_lz_scale<<<R, kBlock, 0, st>>>(pro);
