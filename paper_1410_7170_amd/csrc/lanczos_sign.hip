@@ -221,12 +221,25 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
         OVL_HIP(hipMemcpyAsync(ha.data(), da, sizeof(double) * NR * k, hipMemcpyDeviceToHost, st));
         OVL_HIP(hipMemcpyAsync(hb.data(), db, sizeof(double) * NR * k, hipMemcpyDeviceToHost, st));
         OVL_HIP(hipStreamSynchronize(st));
+        // Each open RHS's T_k, cut where its Krylov space closes; coefficients
+        // that are not finite end the call while nothing is in flight.
+        int open = 0;
+        std::vector<double> a[NR], bt[NR];
+        bool brk[NR] = {};
+        for (int q = 0; q < R; q++) {
+            if (mq[q] != 0) continue;
+            open++;
+            for (int j = 0; j < kc && !brk[q]; j++) {
+                a[q].push_back(ha[(size_t)j * NR + q]);
+                bt[q].push_back(hb[(size_t)j * NR + q]);
+                if (!std::isfinite(a[q][j]) || !std::isfinite(bt[q][j])) return OVL_ERR_NONFINITE;
+                brk[q] = bt[q][j] <= 1e-14 * std::fabs(a[q][j]) + 1e-300;   // invariant subspace: exact
+            }
+        }
         // The device goes on while the host decomposes T_k, by no more steps
         // than that takes (at least 15 ns per row squared of each RHS; a step: its
         // 8 fields and links at 5 TB/s, or 15 us), so that none delays pass 2
         // where this check is the last.
-        int open = 0;
-        for (int q = 0; q < R; q++) open += mq[q] == 0;
         const double host = 15e-9 * k * k * open;
         const double gpu = std::max(15e-6, 2.5e3 * (double)L.V * R / 5e12);
         const int ahead = std::min(std::min(kCheck - 1, kmax - k), (int)(host / gpu));
@@ -235,27 +248,18 @@ int lanczos_sign(const Lat &L, const void *U64, double m0, Fld b, Fld y, double 
         all = true;
         for (int q = 0; q < R; q++) {
             if (mq[q] != 0) continue;
-            std::vector<double> a(kc), bt(kc);
-            bool brk = false;
-            int kk = kc;
-            for (int j = 0; j < kc; j++) {
-                a[j] = ha[(size_t)j * NR + q];
-                bt[j] = hb[(size_t)j * NR + q];
-                if (!std::isfinite(a[j]) || !std::isfinite(bt[j])) return OVL_ERR_NONFINITE;
-                if (bt[j] <= 1e-14 * std::fabs(a[j]) + 1e-300) {   // invariant subspace: exact
-                    kk = j + 1;
-                    brk = true;
-                    break;
-                }
-            }
+            const int kk = (int)a[q].size();
             std::vector<double> cq;
-            if (!tridiag_sign_e1(kk, a.data(), bt.data(), bn[q], cq)) return OVL_ERR_NONFINITE;
+            if (!tridiag_sign_e1(kk, a[q].data(), bt[q].data(), bn[q], cq)) {
+                OVL_HIP(hipStreamSynchronize(st));   // the steps ahead use the caller's memory
+                return OVL_ERR_NONFINITE;
+            }
             double diff = 0.0;
             for (int j = 0; j < kk; j++) {
                 const double o = j < (int)cprev[q].size() ? cprev[q][j] : 0.0;
                 diff += (cq[j] - o) * (cq[j] - o);
             }
-            if (brk || std::sqrt(diff) <= tol * bn[q]) {
+            if (brk[q] || std::sqrt(diff) <= tol * bn[q]) {
                 mq[q] = kk;
                 cbest[q] = cq;
             } else {
