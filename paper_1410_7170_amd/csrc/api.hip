@@ -483,8 +483,9 @@ static int solve_y(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
         // caller's per-shift statistics leave it out
         bool base0 = nshift < NS;
         for (int j = 0; j < nshift; j++) base0 = base0 && shifts[j] > 0.0;
-        o.base_p_only = base0;
+        rc = OVL_ERR_NONFINITE;
         if (base0) {
+            o.base_p_only = true;
             double sh[NS], w[NS];
             sh[0] = w[0] = 0.0;
             for (int j = 0; j < nshift; j++) {
@@ -498,7 +499,12 @@ static int solve_y(const Lat &L, const ovl_gauge *U, double m0, int nshift, cons
                     for (int j = 0; j < nshift; j++) stats->shift_iters[q][j] = stats->shift_iters[q][j + 1];
                     stats->shift_iters[q][nshift] = 0;
                 }
-        } else {
+        }
+        // A source in the kernel of Q leaves that base no step (Q p = 0: its
+        // alpha is not finite), although the shifted systems are as well posed
+        // as ever; their smallest shift is then the base.
+        if (rc == OVL_ERR_NONFINITE) {
+            o.base_p_only = false;
             rc = mscg_blocked_t<P_F64>(L, U, m0, nshift, shifts, weights, b, y, o, prm, stats, ws + yb,
                                        ws_bytes - yb, st, scr);
         }
