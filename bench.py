@@ -11,7 +11,8 @@ oracle's stored samples of the same apply (tests/golden), for the error line.
 
 Besides the timed steps the line reports: the stencil's bandwidth in each
 precision; the FP64 forms' applies/s (the speedups are against the fastest of
-them, with the default FP64 parameters' ratio kept as a second key); the timed result's
+them, with the plain form's ratio kept as a second key; the differences are
+against the plain form, which shares least with the others); the timed result's
 error against the FP64 oracle at the sampled sites and its Ginsparg-Wilson
 residual; the 16^3x32 workload (operator bandwidth, overlap applies); the
 batched 24^3x48 point-source workload; and the oracle's own speed on the
@@ -169,6 +170,8 @@ def params_for(ovl, form, tol, profile=False):
         prm = params_for(ovl, form, tol, profile)
         prm.block = int(m)
         return prm
+    if form == "fp64_plain":  # every shifted vector in every iteration, and the verification that asks for it
+        return ovl.default_params(tol=tol, maxiter=5000, profile=int(profile), verify=1)
     if form == "fp64":       # FP64 with the default parameters (block = 0)
         return ovl.default_params(tol=tol, maxiter=5000, profile=int(profile))
     if form == "fp64_blocked":
@@ -259,8 +262,8 @@ def main():
     # ---- the reference forms, each timed over a few applies
     forms = [f for f in args.forms.split(",") if f]
     timed_form = "mixed" if args.form == "auto" else args.form
-    if "fp64" not in forms:
-        forms.insert(0, "fp64")
+    if "fp64_plain" not in forms:
+        forms.insert(0, "fp64_plain")
     results, outputs = {}, {}
     for form in forms:
         st = overlap(form)
@@ -275,7 +278,7 @@ def main():
                              max_true_residual=max(st["true_residual"][0]))
         outputs[form] = out.to_canonical().cpu().numpy()
         log(f"form {form}: {len(b) / results[form]['seconds']:.3f} applies/s, {st['iterations']} iterations")
-    ref = outputs["fp64"]
+    ref = outputs["fp64_plain"]
     for form in forms:
         results[form]["rel_diff_vs_fp64"] = float(np.linalg.norm(outputs[form] - ref) / np.linalg.norm(ref))
 
@@ -327,7 +330,7 @@ def main():
         checks = accuracy_checks(args, ovl, torch, np, lat, B, out, got, overlap, timed_form)
 
     nrhs = len(b)
-    fp64_rate = nrhs / results["fp64"]["seconds"]
+    plain_rate = nrhs / results["fp64_plain"]["seconds"]
     best64 = min((f for f in results if f.startswith("fp64")), key=lambda f: results[f]["seconds"])
     best64_rate = nrhs / results[best64]["seconds"]
 
@@ -345,7 +348,7 @@ def main():
     # ---- CPU baseline: the FP64 oracle on a bounded sample of the same workload
     cpu = None
     if not args.no_cpu_baseline:
-        cpu = cpu_baseline(args, dims, U, b[0], shifts, weights, results["fp64"]["shift_iters"])
+        cpu = cpu_baseline(args, dims, U, b[0], shifts, weights, results["fp64_plain"]["shift_iters"])
 
     # one unpack and one pack of a packed FP64 field: plain streaming kernels
     # of known size for counter calibration
@@ -380,7 +383,7 @@ def main():
         "fp64_applies_per_s": round(best64_rate, 4),
         "fp64_form": best64,
         "speedup_vs_fp64": round(applies_per_s / best64_rate, 3),
-        "speedup_vs_fp64_plain": round(applies_per_s / fp64_rate, 3),
+        "speedup_vs_fp64_plain": round(applies_per_s / plain_rate, 3),
         "iterations": last["iterations"],
         "timed_max_true_residual": max(max(r) for r in last["true_residual"][:nrhs]),
         "timed_refine_iterations": last["refine_iterations"],
@@ -492,7 +495,7 @@ def small_line(args, ovl, synth, np, torch):
     B = ovl.Spinor.from_canonical(lat, torch.from_numpy(b).cuda(), ovl.F64)
     out = ovl.Spinor(lat, ovl.F64)
     rates = {}
-    for form in ("fp64", "fp64_blocked", "mixed", "lanczos"):
+    for form in ("fp64_plain", "fp64", "fp64_blocked", "mixed", "lanczos"):
         prm = params_for(ovl, form, args.tol)
         ovl.overlap_apply(lat, G, RHO, shifts, weights, B, out, prm)
         torch.cuda.synchronize()
@@ -702,7 +705,7 @@ def multi_rhs_line(args, ovl, synth, np, torch):
     B1 = ovl.Spinor.from_canonical(lat, torch.from_numpy(b[:1]).cuda(), ovl.F64)
     out1 = ovl.Spinor(lat, ovl.F64)
     single = {}
-    for form in ("fp64_blocked", "fp64"):
+    for form in ("fp64_blocked", "fp64_plain"):
         p64 = params_for(ovl, form, args.tol)
         ovl.overlap_apply(lat, G, RHO, shifts, weights, B1, out1, p64)
         torch.cuda.synchronize()
@@ -717,9 +720,9 @@ def multi_rhs_line(args, ovl, synth, np, torch):
                 nrhs=B.nrhs, form="mixed (FP64 until the hand-over, FP32 bulk, FP64 verification)",
                 applies_per_s=round(rate, 4), seconds_per_batch=round(el / args.multi_rhs_steps, 4),
                 fp64_single_rhs_applies_per_s=round(single["fp64_blocked"], 4),
-                fp64_plain_single_rhs_applies_per_s=round(single["fp64"], 4),
+                fp64_plain_single_rhs_applies_per_s=round(single["fp64_plain"], 4),
                 speedup_vs_fp64_single_rhs=round(rate / single["fp64_blocked"], 3),
-                speedup_vs_fp64_plain_single_rhs=round(rate / single["fp64"], 3),
+                speedup_vs_fp64_plain_single_rhs=round(rate / single["fp64_plain"], 3),
                 iterations=st["iterations"], max_true_residual=max(max(r) for r in st["true_residual"]),
                 refine_iterations=st["refine_iterations"],
                 rel_diff_rhs0_vs_fp64=float(np.linalg.norm(got - ref) / np.linalg.norm(ref)),
