@@ -193,7 +193,11 @@ typedef struct {
     int32_t refine;          /* mixed: verify each shift in FP64 and refine
                                 those above tol (1) or only report (0) */
     int32_t verify;          /* FP64 mode: also compute every shift's FP64 true
-                                residual into stats (2 FP64 stencils per shift) */
+                                residual into stats (2 FP64 stencils per shift).
+                                A weighted sum is then formed from the x_j that
+                                were verified; with block = 0 these are the plain
+                                form's, which differ from what the same call
+                                without verify sums (block) by rounding only */
     int32_t profile;         /* time the solver's kernels with HIP events on
                                 the call's stream and fill the kernel_* stats:
                                 1 every class, 2 the stencils only (each timed
