@@ -118,9 +118,9 @@ int site_blocks(const Lat &L);           // blocks of a flat elementwise launch 
 // Launch shape of a stencil of precision prec on nrhs fields.  ts > 0: the
 // time-streaming form with ts slices per thread, blocks of nt threads, K = 2^kr
 // lanes per site (RHS tile) and nt >> kr sites per block; ts = 0: one thread
-// per site and RHS, in blocks of nt where they leave partial sums.  blocks_per_tile: blocks of one RHS tile (each fills one
-// partial-sum slot per RHS of the tile).
-// ts = 0 and tile.nt > 0: the tile form.
+// per site and RHS, in blocks of nt where they leave partial sums.
+// blocks_per_tile: blocks of one RHS tile (each fills one partial-sum slot per
+// RHS of the tile).  ts = 0 and tile.nt > 0: the tile form.
 struct StencilShape {
     int ts, nt, kr, blocks_per_tile, ntile;
     Tile tile;

@@ -105,8 +105,8 @@ __global__ __launch_bounds__(kBlock) void k_unpack_spinor(Geom g, int64_t V, con
 // read, 1.4 written); one pass takes 541 us (4.8 TB/s).
 constexpr int kPackSites = 64;   // 8 runs (parity, direction) of 32 pairs of x3 neighbours: 256 threads
 
-__global__ __launch_bounds__(kBlock) void k_pack_gauge(Geom g, int64_t V, const double2 *canon, double2 *o64, float4 *o32,
-                                                        uint2 *o16)
+__global__ __launch_bounds__(kBlock) void k_pack_gauge(Geom g, int64_t V, const double2 *canon, double2 *o64,
+                                                        float4 *o32, uint2 *o16)
 {
     __shared__ double2 lds[24][kPackSites + 1];
     const int64_t first = (int64_t)blockIdx.x * kPackSites;
@@ -188,7 +188,8 @@ hipError_t launch_unpack_spinor(const Lat &L, Fld in, void *canon, hipStream_t s
 hipError_t launch_pack_gauge(const Lat &L, const void *canon, void *f64, void *f32, void *f16, hipStream_t st)
 {
     dim3 grid((unsigned)((L.V + kPackSites - 1) / kPackSites));
-    k_pack_gauge<<<grid, kBlock, 0, st>>>(L.g, L.V, (const double2 *)canon, (double2 *)f64, (float4 *)f32, (uint2 *)f16);
+    k_pack_gauge<<<grid, kBlock, 0, st>>>(L.g, L.V, (const double2 *)canon, (double2 *)f64, (float4 *)f32,
+                                          (uint2 *)f16);
     return hipGetLastError();
 }
 

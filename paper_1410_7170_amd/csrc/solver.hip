@@ -276,8 +276,9 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
             prof.pair(OVL_K_SCALAR, &v0, &v1);
             launch_k(k_ms_beta, dim3(R), dim3(kBlock), st, v0, v1, pb);
             prof.pair(OVL_K_UPDATE, &v0, &v1);
-            launch_k(k_ms_update<P_F64>, dim3(nblk, R, elem_split(nblk * R, nshift)), dim3(kBlock), st, v0, v1, L.g, L.nb, (const MState *)S,
-                     (const void *)r.d, (const float *)nullptr, pfl.d, (float *)nullptr, x.d, (float *)nullptr, R);
+            launch_k(k_ms_update<P_F64>, dim3(nblk, R, elem_split(nblk * R, nshift)), dim3(kBlock), st, v0, v1, L.g,
+                     L.nb, (const MState *)S, (const void *)r.d, (const float *)nullptr, pfl.d, (float *)nullptr,
+                     x.d, (float *)nullptr, R);
             OVL_HIP(hipGetLastError());
             stencils += 2;
         }

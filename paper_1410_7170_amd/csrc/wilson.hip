@@ -1,5 +1,6 @@
 // Launch of the Wilson stencil kernels (wilson.h, wilson_tile.h): blocks of 64 or
-// 256 sites (192 or 256 for the streaming form, up to 512 for the tile form), ordered (site block, RHS) and spread over the XCDs by the kernel itself.
+// 256 sites (192 or 256 for the streaming form, up to 512 for the tile form),
+// ordered (site block, RHS) and spread over the XCDs by the kernel itself.
 #include <algorithm>
 #include <cmath>
 
@@ -104,17 +105,26 @@ static StencilShape stencil_shape_ts(const Lat &L, int ts, int nrhs)
     return sh;
 }
 
-// The tile of a lattice's tile form.  Below 131072 sites tiles give a CU too
-// little to overlap (FP64 D_W at 16^4: 14.5 us with one site per thread, 13.6
-// with tiles; 28x14^2x16: 21 and 27) and there are none.  Rows of x3 stay whole
-// up to 32 sites (a row is then whole 128-byte lines or nearly so); the other
-// extents are divisors of the lattice's, and the choice follows a sweep over
-// eight lattices of 131072 to 663552 sites: x2, whose neighbours are the nearest
-// blocks, at least 2 (48x22^3: 115 us with 4x2x2x22, 137 with 4x2x1x22), time
-// about 4, x1 least of all; and blocks that fill the last round of a CU's 512
-// threads (40x18^3: 47 us at 2.8 rounds, 50 at 2.1).  The best tiles then take
-// 0.67 to 0.88 of the one-site form's time, one field or three; 48x22^3 with
-// three fields alone is 2% behind.
+// The tile of a lattice's tile form.  From 131072 sites on (a 512-site tile for
+// each of 256 CUs) every lattice measured gains, below it some lose and there
+// are none (one site per thread / tiles: FP64 D_W, mixed overlap apply):
+//   16^4      13.7 / 16.1 us    5.80 / 6.21 ms     65536 sites
+//   28x14^2x16 16.4 / 17.0      7.87 / 7.83        87808
+//   24x16^3   17.6 / 19.1       7.94 / 8.15        98304
+//   18^4      23.4 / 21.0       9.30 / 9.04       104976
+//   28x16^3   23.5 / 20.9       8.90 / 8.73       114688
+//   20x18^3   26.7 / 28.0       9.68 / 10.81      116640
+//   32x16^3   32.2 / 23.1      10.56 / 9.84       131072
+//   24x18^3   35.0 / 31.0      13.77 / 13.36      139968
+//   20x18x22^2 45.2 / 37.5     15.18 / 15.10      174240
+// Rows of x3 stay whole up to 32 sites (a row is then whole 128-byte lines or
+// nearly so); the other extents are divisors of the lattice's, and the choice
+// follows a sweep over eight lattices of 131072 to 663552 sites: x2, whose
+// neighbours are the nearest blocks, at least 2 (48x22^3: 115 us with 4x2x2x22,
+// 137 with 4x2x1x22), time about 4, x1 least of all; and blocks that fill the last
+// round of a CU's 512 threads (40x18^3: 47 us at 2.8 rounds, 50 at 2.1).  The best
+// tiles then take 0.67 to 0.88 of the one-site form's time, one field or three;
+// 48x22^3 with three fields alone is 2% behind.
 constexpr int64_t kTileSites = 512 * 256;
 
 Tile pick_tile(const int E[4], int64_t V)
@@ -156,21 +166,17 @@ Tile pick_tile(const int E[4], int64_t V)
 
 static int tile_count(const Tile &t) { return t.N[0] * t.N[1] * t.N[2] * t.N[3]; }
 
-// 48-bit fields take the FP64 length, halved while the launch has fewer than
-// 512 blocks: their staged build runs two waves per SIMD (below), which needs
-// two blocks per CU (at 32^3x64: 16 slices and 512 blocks, the mixed solver's
-// 48-bit stencils 381 -> 367 us (t update) and 382 -> 353 us (residual
-// update) against one wave at 32 slices; FP64 itself spills at two waves and
-// keeps one)
 // Blocks of the one-site form: one wave each where a launch leaves no partial
 // sums, so that they spread evenly over the CUs (a wave reads 70 to 150 KB
 // through its CU's L1: D_W at 12^3x20 with 4 RHS FP64 26.8 us with four waves a
 // block, 22.5 with one, FP32 13.0 and 10.0; 22x20x22x24 with 2 RHS FP32 39.0 and
 // 38.2).  With partial sums up to kWaveSites sites, whose sums are then at most
-// one slot to each of the 256 strided sums: the 4^3x8 overlap apply 3.87 and
-// 3.52 ms, 12x8x6x16 multishift 4.75 and 4.17, but at 12^3x18, where every wave
-// would add up 486 slots, 5.51 and 5.67 ms.  The two waves per parity of 4^4
-// gain nothing apart (Q^2 12.7 and 12.9 us).
+// one slot to each of the 256 strided sums; beyond, every wave of a carried
+// stage adds up more (four waves a block / one, FP64 and mixed overlap apply, ms:
+// 8x12^3 3.77 / 3.42, 3.55 / 3.57; 10x12^3 4.06 / 3.90, 3.79 / 3.94;
+// 12^4 4.15 / 4.12, 3.95 / 4.23; 20x12^3 5.25 / 6.05, 4.70 / 5.80).  The two waves
+// per parity of 4^4 gain nothing apart, those of anything larger do (Q^2 in us:
+// 4^4 12.95 / 13.1, 6x4^3 13.8 / 12.8, 8x4^3 15.3 / 13.7, 6^4 17.2 / 14.3).
 constexpr int64_t kWaveSites = 64 * 256;
 constexpr int64_t kTwoWaves = 256;
 
@@ -187,6 +193,12 @@ static bool mode_sums(int mode)
 
 static int blocks_of(const Lat &L, int nt) { return 2 * ((L.Vh + nt - 1) / nt); }
 
+// 48-bit fields take the FP64 length, halved while the launch has fewer than
+// 512 blocks: their staged build runs two waves per SIMD (wilson_ts_dispatch),
+// which needs two blocks per CU (at 32^3x64: 16 slices and 512 blocks, the mixed
+// solver's 48-bit stencils 381 -> 367 us (t update) and 382 -> 353 us (residual
+// update) against one wave at 32 slices; FP64 itself spills at two waves and
+// keeps one)
 StencilShape stencil_shape(const Lat &L, int prec, int nrhs)
 {
     const int ts = (prec == P_F64 || prec == P_F48) && L.g.Ts64 > 0 ? L.g.Ts64 : L.g.Ts;
@@ -214,8 +226,14 @@ int part_stride(const Lat &L)
 }
 
 // Every block of a carrying launch adds up all of the previous one's partial
-// sums: cheap up to the 512 blocks of 16^3x32, but their reads grow with the
-// square of the lattice
+// sums, and their reads grow with the square of the lattice; up to two slots for
+// each of the 256 strided sums a launch that carries is faster everywhere (stages
+// in kernels of their own / carried, FP64 and mixed overlap apply, ms: 16x10^3
+// 4.53 / 3.94, 4.69 / 4.01; 20x16^3 10.4 / 9.23, 8.61 / 7.34; 32x16^3 13.3 / 12.1,
+// 11.0 / 9.81; 24x18^3, 486 slots, 16.6 / 15.4, 13.8 / 13.3).  Beyond, tiles of
+// 512 threads would still gain (24x22^3, 726 slots: 26.1 / 25.2, 21.2 / 20.2;
+// 28x22^3, 968: 31.7 / 31.2, 27.3 / 26.2), those of 256 with several RHS lose
+// (26x22^2x20, 1573 slots, mixed: 21.7 / 21.1, 3 RHS 51.9 / 52.8).
 bool carries_scalars(const Lat &L, int prec, int nrhs)
 {
     return stencil_shape(L, prec, nrhs).ts == 0 && stencil_partials(L, prec, nrhs) <= 512;

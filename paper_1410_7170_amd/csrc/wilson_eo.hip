@@ -386,7 +386,8 @@ __global__ __launch_bounds__(kBlock) void k_eo_step(int Vh, int S, EoState *st, 
 // e += alpha p, p = z + beta p (FP32 even halves), one thread per site; pz, ps
 // as pq of k_eo_step.  Bound by its five fields.
 __global__ __launch_bounds__(kBlock) void k_eo_turn(int Vh, int S, EoState *st, const double *pz, int nz,
-                                                     const double *ps, int ns, int it, const float4 *z, float4 *p, float4 *e)
+                                                     const double *ps, int ns, int it, const float4 *z, float4 *p,
+                                                     float4 *e)
 {
     __shared__ double lds[8];
     if (st->stop && st->stop < 2 * it + 2) return;
@@ -544,8 +545,8 @@ int wilson_solve_eo(const Lat &L, const ovl_gauge *U, double m0, Fld b, Fld x, d
                                                                 done, st, 1)));
                     OVL_HIP((eo_hop<P_F32, false, true, true>(L, 0, Sf, Sf, Zf, U->f32, A, -0.5, p0, done, st)));
                     if (!carry) k_eo_beta<<<1, kBlock, 0, st>>>(es, p0, nh, p1, ns, it);
-                    k_eo_turn<<<gv, kBlock, 0, st>>>(Vh, S, es, carry ? p0 : nullptr, nh, p1, ns, it, (const float4 *)Zf,
-                                                      (float4 *)Pf, (float4 *)Ef);
+                    k_eo_turn<<<gv, kBlock, 0, st>>>(Vh, S, es, carry ? p0 : nullptr, nh, p1, ns, it,
+                                                      (const float4 *)Zf, (float4 *)Pf, (float4 *)Ef);
                     OVL_HIP(hipGetLastError());
                 }
                 EoState h;

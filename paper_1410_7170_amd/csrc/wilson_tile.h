@@ -104,7 +104,8 @@ template <int MU, bool FWD>
 __device__ __forceinline__ int nb_lex(const Geom &g, const TileSite &s)
 {
     const int L = g.L[MU], wrap = (L - 1) * s.gs[MU];
-    return FWD ? (s.x[MU] == L - 1 ? s.lex - wrap : s.lex + s.gs[MU]) : (s.x[MU] == 0 ? s.lex + wrap : s.lex - s.gs[MU]);
+    return FWD ? (s.x[MU] == L - 1 ? s.lex - wrap : s.lex + s.gs[MU])
+               : (s.x[MU] == 0 ? s.lex + wrap : s.lex - s.gs[MU]);
 }
 
 template <int MU, bool FWD>
@@ -115,7 +116,8 @@ __device__ __forceinline__ void link_tile(const Geom &g, const GaugeRef<P_F64> &
 
 template <int PREC, int MU, bool FWD, int NT>
 __device__ __forceinline__ void hop_tile(const Geom &g, const Tile &tl, const SpinorRef<PREC> &in,
-                                         const Stage<PREC, NT> &st, const TileSite &t, const RawLink &r, cplx<double> acc[4][3])
+                                         const Stage<PREC, NT> &st, const TileSite &t, const RawLink &r,
+                                         cplx<double> acc[4][3])
 {
     cplx<double> s[4][3], u[3][3];
     const int Tm = tl.T[MU], lw = (Tm - 1) * t.ls[MU];

@@ -54,7 +54,8 @@ int main()
         alpha_stage<64>(pa, 0, lds);
         check(!before && sits_out(pa, st.skip, 0) == before, "alpha stage: sites see one answer");
         const bool good = tt == 0.5;
-        check(st.run_c[0] == good && st.nonfinite[0] == !good && st.alpha[0] == (good ? 2.0 : 1.0), "alpha stage: state");
+        check(st.run_c[0] == good && st.nonfinite[0] == !good && st.alpha[0] == (good ? 2.0 : 1.0),
+              "alpha stage: state");
         // the next launch carries beta: its sites take part only after a good alpha
         sum = 0.25;
         const bool beta_before = sits_out(pb, st.skip, 0);
