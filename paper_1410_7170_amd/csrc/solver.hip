@@ -55,16 +55,21 @@ __global__ __launch_bounds__(kBlock) void k_ms_beta(ProArgs a)
     beta_stage<kBlock>(a, blockIdx.x, lds);
 }
 
-// Shift update, FP64 fields.  Fields: r [nrhs], p and x [nshift][nrhs].  The
-// grid's z deals the shifts out (elem_split): at 8x4^3, 20 shifts, one block
-// after another took 20 us.
-template <int PREC>
+// Parts into which the shift update deals out the shifts: up to 384 blocks in
+// all.  Each part reads r again, so more of them lose (24 shifts, multishift with
+// one part / up to 512 / 1024 blocks, ms: 8x4^3 6.9 / 4.4 / 4.4, 16x8^3 8.9 / 6.4 / 6.4,
+// 24x12^3, 162 blocks, 15.4 / 14.9 / 15.2, 20x14x18x10, 198, 18.2 / 18.4 / 18.4).
+static int update_parts(int blocks, int nshift) { return std::max(1, std::min(nshift, 384 / blocks)); }
+
+// Shift update, FP64 fields.  Fields: r [nrhs], p and x [nshift][nrhs].  SPLIT:
+// the grid's z deals the shifts out.
+template <int PREC, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_ms_update(Geom g, int nb, const MState *st, const void *rf, const float *rsc,
                                                       void *pf, float *psc, void *xf, float *xsc, int nrhs)
 {
     using T = typename Real<PREC>::T;
     const int r = blockIdx.y;
-    const int ns = st->nshift, j0 = blockIdx.z, js = gridDim.z;
+    const int ns = st->nshift, j0 = SPLIT ? blockIdx.z : 0, js = SPLIT ? gridDim.z : 1;
     int any = 0;
     for (int j = j0; j < ns; j += js) any |= st->act_cur[r][j];
     if (!any) return;
@@ -254,6 +259,7 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
     const ProArgs pa{PRO_ALPHA, npart, pstr, R, s0 != 0.0, partials, S, nullptr, 0.0, 0};
     const ProArgs pb{PRO_BETA, npart, pstr, R, 0, partials, S, nullptr, 0.0, 0};
 
+    const int parts = update_parts(nblk * R, nshift);
     const int check = prm->check_every > 0 ? prm->check_every : 10;
     int it = 0;
     int stencils = 0;
@@ -276,9 +282,9 @@ int mscg_f64(const Lat &L, const void *U64, double m0, int nshift, const double 
             prof.pair(OVL_K_SCALAR, &v0, &v1);
             launch_k(k_ms_beta, dim3(R), dim3(kBlock), st, v0, v1, pb);
             prof.pair(OVL_K_UPDATE, &v0, &v1);
-            launch_k(k_ms_update<P_F64>, dim3(nblk, R, elem_split(nblk * R, nshift)), dim3(kBlock), st, v0, v1, L.g,
-                     L.nb, (const MState *)S, (const void *)r.d, (const float *)nullptr, pfl.d, (float *)nullptr,
-                     x.d, (float *)nullptr, R);
+            launch_k(parts > 1 ? k_ms_update<P_F64, true> : k_ms_update<P_F64, false>, dim3(nblk, R, parts),
+                     dim3(kBlock), st, v0, v1, L.g, L.nb, (const MState *)S, (const void *)r.d,
+                     (const float *)nullptr, pfl.d, (float *)nullptr, x.d, (float *)nullptr, R);
             OVL_HIP(hipGetLastError());
             stencils += 2;
         }
