@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "tile_plan.h"
+
 namespace ovl {
 
 constexpr int kBlock = 256;     // threads per block of every site-parallel kernel
@@ -86,15 +88,6 @@ struct Geom {
     int Ts64;      // time slices per thread of the FP64 streaming stencil (0: Ts)
     int Kr;        // log2 of the RHS tile of the streaming stencil (lanes per site)
     int Mfma;      // FP32 D_W on several RHS by the matrix-core stencil
-};
-
-// A tile of the stencil's tile form (wilson_tile.h): its extents, the tiles per
-// direction and the multipliers that divide by the extents (n / d = n * m >> 20,
-// exact for n < 512 and d <= 512).  nt threads a block; nt = 0: no tiles.
-struct Tile {
-    int T[4], N[4];
-    unsigned m3, m2, m1;
-    int nt;
 };
 
 // Threads (sites) per block of the time-streaming stencil with ts slices per

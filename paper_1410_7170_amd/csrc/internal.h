@@ -120,13 +120,13 @@ int site_blocks(const Lat &L);           // blocks of a flat elementwise launch 
 // lanes per site (RHS tile) and nt >> kr sites per block; ts = 0: one thread
 // per site and RHS, in blocks of nt where they leave partial sums.
 // blocks_per_tile: blocks of one RHS tile (each fills one partial-sum slot per
-// RHS of the tile).  ts = 0 and tile.nt > 0: the tile form.
+// RHS of the tile).  ts = 0 and tile.nt > 0: the tile form.  sums: of a launch that
+// leaves partial sums, or of a Lanczos pass.
 struct StencilShape {
     int ts, nt, kr, blocks_per_tile, ntile;
     Tile tile;
 };
-StencilShape stencil_shape(const Lat &L, int prec, int nrhs);
-Tile pick_tile(const int E[4], int64_t V);
+StencilShape stencil_shape(const Lat &L, int prec, int nrhs, bool sums = true);
 // Partial-sum slots that a stencil launch of this precision on nrhs fields
 // fills, and the row stride (slots allocated) of its partials.
 int stencil_partials(const Lat &L, int prec, int nrhs);

@@ -2,7 +2,6 @@
 // 256 sites (192 or 256 for the streaming form, up to 512 for the tile form),
 // ordered (site block, RHS) and spread over the XCDs by the kernel itself.
 #include <algorithm>
-#include <cmath>
 
 #include "internal.h"
 
@@ -105,67 +104,6 @@ static StencilShape stencil_shape_ts(const Lat &L, int ts, int nrhs)
     return sh;
 }
 
-// The tile of a lattice's tile form.  From 131072 sites on (a 512-site tile for
-// each of 256 CUs) every lattice measured gains, below it some lose and there
-// are none (one site per thread / tiles: FP64 D_W, mixed overlap apply):
-//   16^4      13.7 / 16.1 us    5.80 / 6.21 ms     65536 sites
-//   28x14^2x16 16.4 / 17.0      7.87 / 7.83        87808
-//   24x16^3   17.6 / 19.1       7.94 / 8.15        98304
-//   18^4      23.4 / 21.0       9.30 / 9.04       104976
-//   28x16^3   23.5 / 20.9       8.90 / 8.73       114688
-//   20x18^3   26.7 / 28.0       9.68 / 10.81      116640
-//   32x16^3   32.2 / 23.1      10.56 / 9.84       131072
-//   24x18^3   35.0 / 31.0      13.77 / 13.36      139968
-//   20x18x22^2 45.2 / 37.5     15.18 / 15.10      174240
-// Rows of x3 stay whole up to 32 sites (a row is then whole 128-byte lines or
-// nearly so); the other extents are divisors of the lattice's, and the choice
-// follows a sweep over eight lattices of 131072 to 663552 sites: x2, whose
-// neighbours are the nearest blocks, at least 2 (48x22^3: 115 us with 4x2x2x22,
-// 137 with 4x2x1x22), time about 4, x1 least of all; and blocks that fill the last
-// round of a CU's 512 threads (40x18^3: 47 us at 2.8 rounds, 50 at 2.1).  The best
-// tiles then take 0.67 to 0.88 of the one-site form's time, one field or three;
-// 48x22^3 with three fields alone is 2% behind.
-constexpr int64_t kTileSites = 512 * 256;
-
-Tile pick_tile(const int E[4], int64_t V)
-{
-    Tile best{};
-    if (V < kTileSites) return best;
-    int t3 = 0;
-    for (int d = std::min(32, E[3]); d > 0 && !t3; d--)
-        if (E[3] % d == 0 && (d == E[3] || d % 8 == 0)) t3 = d;
-    for (int d = std::min(32, E[3]); d > 0 && !t3; d--)
-        if (E[3] % d == 0) t3 = d;
-    double least = 1e300;
-    for (int nt : {512, 256})
-        for (int t2 = 1; t2 <= std::min(8, E[2]) && t2 * t3 <= nt; t2++) {
-            if (E[2] % t2) continue;
-            for (int t1 = 1; t1 <= std::min(8, E[1]) && t1 * t2 * t3 <= nt; t1++) {
-                if (E[1] % t1) continue;
-                for (int t0 = 1; t0 <= std::min(8, E[0]) && t0 * t1 * t2 * t3 <= nt; t0++) {
-                    if (E[0] % t0 || 2 * t0 * t1 * t2 * t3 <= nt) continue;
-                    const Tile t{{t0, t1, t2, t3}, {E[0] / t0, E[1] / t1, E[2] / t2, E[3] / t3}, 0, 0, 0, nt};
-                    const double rounds = (double)t.N[0] * t.N[1] * t.N[2] * t.N[3] * nt / (256 * 512);
-                    const double cost = (3.0 + 1.5 / t0 + 0.05 * t0 + 0.7 / t1 + 2.5 / t2) *
-                                        std::sqrt(std::ceil(rounds) / rounds);
-                    if (cost < least) {
-                        least = cost;
-                        best = t;
-                    }
-                }
-            }
-        }
-    auto inverse = [](int d) { return (unsigned)(((1u << 20) + d - 1) / d); };
-    if (best.nt) {
-        best.m3 = inverse(best.T[3]);
-        best.m2 = inverse(best.T[2]);
-        best.m1 = inverse(best.T[1]);
-    }
-    return best;
-}
-
-static int tile_count(const Tile &t) { return t.N[0] * t.N[1] * t.N[2] * t.N[3]; }
-
 // Blocks of the one-site form: one wave each where a launch leaves no partial
 // sums, so that they spread evenly over the CUs (a wave reads 70 to 150 KB
 // through its CU's L1: D_W at 12^3x20 with 4 RHS FP64 26.8 us with four waves a
@@ -193,18 +131,29 @@ static bool mode_sums(int mode)
 
 static int blocks_of(const Lat &L, int nt) { return 2 * ((L.Vh + nt - 1) / nt); }
 
+// Every block of a carrying launch adds up all of the previous one's partial
+// sums, and their reads grow with the square of the lattice; up to two slots for
+// each of the 256 strided sums a launch that carries is faster everywhere (stages
+// in kernels of their own / carried, FP64 and mixed overlap apply, ms: 16x10^3
+// 4.53 / 3.94, 4.69 / 4.01; 20x16^3 10.4 / 9.23, 8.61 / 7.34; 32x16^3 13.3 / 12.1,
+// 11.0 / 9.81; 24x18^3, 432 slots, 16.6 / 15.4, 13.8 / 13.3).  Beyond, several RHS
+// can lose (26x22^2x20, tiles, 1573 slots, mixed: 21.7 / 21.1, 3 RHS 51.9 / 52.8).
+constexpr int kCarrySlots = 512;
+
 // 48-bit fields take the FP64 length, halved while the launch has fewer than
 // 512 blocks: their staged build runs two waves per SIMD (wilson_ts_dispatch),
 // which needs two blocks per CU (at 32^3x64: 16 slices and 512 blocks, the mixed
 // solver's 48-bit stencils 381 -> 367 us (t update) and 382 -> 353 us (residual
 // update) against one wave at 32 slices; FP64 itself spills at two waves and
 // keeps one)
-StencilShape stencil_shape(const Lat &L, int prec, int nrhs)
+StencilShape stencil_shape(const Lat &L, int prec, int nrhs, bool sums)
 {
     const int ts = (prec == P_F64 || prec == P_F48) && L.g.Ts64 > 0 ? L.g.Ts64 : L.g.Ts;
     if (ts <= 0 || prec == P_F16S) {
         StencilShape sh{};
-        if (prec == P_F64 || prec == P_F48) sh.tile = L.tile;
+        if ((prec == P_F64 || prec == P_F48) &&
+            tile_pays(L.tile, prec == P_F64, nrhs, sums, tile_count(L.tile) <= kCarrySlots))
+            sh.tile = L.tile;
         sh.nt = site_threads(L, true);
         return sh;
     }
@@ -225,18 +174,9 @@ int part_stride(const Lat &L)
     return std::max(blocks_of(L, site_threads(L, true)), L.tile.nt ? tile_count(L.tile) : 0);
 }
 
-// Every block of a carrying launch adds up all of the previous one's partial
-// sums, and their reads grow with the square of the lattice; up to two slots for
-// each of the 256 strided sums a launch that carries is faster everywhere (stages
-// in kernels of their own / carried, FP64 and mixed overlap apply, ms: 16x10^3
-// 4.53 / 3.94, 4.69 / 4.01; 20x16^3 10.4 / 9.23, 8.61 / 7.34; 32x16^3 13.3 / 12.1,
-// 11.0 / 9.81; 24x18^3, 486 slots, 16.6 / 15.4, 13.8 / 13.3).  Beyond, tiles of
-// 512 threads would still gain (24x22^3, 726 slots: 26.1 / 25.2, 21.2 / 20.2;
-// 28x22^3, 968: 31.7 / 31.2, 27.3 / 26.2), those of 256 with several RHS lose
-// (26x22^2x20, 1573 slots, mixed: 21.7 / 21.1, 3 RHS 51.9 / 52.8).
 bool carries_scalars(const Lat &L, int prec, int nrhs)
 {
-    return stencil_shape(L, prec, nrhs).ts == 0 && stencil_partials(L, prec, nrhs) <= 512;
+    return stencil_shape(L, prec, nrhs).ts == 0 && stencil_partials(L, prec, nrhs) <= kCarrySlots;
 }
 
 template <int PREC, int MODE, bool G5>
@@ -309,7 +249,7 @@ hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hip
         if (h == hipSuccess && e1) return hipEventRecord(e1, st);
         return h;
     }
-    const StencilShape sh = stencil_shape(L, prec, a.nrhs);
+    const StencilShape sh = stencil_shape(L, prec, a.nrhs, mode_sums(mode) || mode >= W_LZ1);
     if (sh.ts > 0) {
         // time-streaming form (FP64, 48-bit, FP32): blocks_per_tile blocks per RHS
         // tile; the FP16 stencil keeps one site per thread, which measured
