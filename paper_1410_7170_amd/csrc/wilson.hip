@@ -105,22 +105,27 @@ static StencilShape stencil_shape_ts(const Lat &L, int ts, int nrhs)
 }
 
 // Blocks of the one-site form: one wave each where a launch leaves no partial
-// sums, so that they spread evenly over the CUs (a wave reads 70 to 150 KB
-// through its CU's L1: D_W at 12^3x20 with 4 RHS FP64 26.8 us with four waves a
-// block, 22.5 with one, FP32 13.0 and 10.0; 22x20x22x24 with 2 RHS FP32 39.0 and
-// 38.2).  With partial sums up to kWaveSites sites, whose sums are then at most
-// one slot to each of the 256 strided sums; beyond, every wave of a carried
-// stage adds up more (four waves a block / one, FP64 and mixed overlap apply, ms:
+// sums and has no more than kWaveWork sites on all its fields, so that they spread
+// evenly over the CUs (a wave reads 70 to 150 KB through its CU's L1: D_W at 12^3x20
+// with 4 RHS FP64 26.8 us with four waves a block, 22.5 with one, FP32 13.0 and
+// 10.0; at 140000 sites 1.24 times as fast in FP32, 1.13 in FP64; from 280000 on
+// 0.97 to 1.01; on 48-bit fields 1.03 to 1.08 at 105000 sites, 0.91 to 1.10 from
+// 131072 on).  With partial sums up to kWaveSites
+// sites, whose sums are then at most one slot to each of the 256 strided sums;
+// beyond, every wave of a carried stage adds up more (four waves a block / one,
+// FP64 and mixed overlap apply, ms:
 // 8x12^3 3.77 / 3.42, 3.55 / 3.57; 10x12^3 4.06 / 3.90, 3.79 / 3.94;
 // 12^4 4.15 / 4.12, 3.95 / 4.23; 20x12^3 5.25 / 6.05, 4.70 / 5.80).  The two waves
 // per parity of 4^4 gain nothing apart, those of anything larger do (Q^2 in us:
 // 4^4 12.95 / 13.1, 6x4^3 13.8 / 12.8, 8x4^3 15.3 / 13.7, 6^4 17.2 / 14.3).
 constexpr int64_t kWaveSites = 64 * 256;
+constexpr int64_t kWaveWork = 1 << 18, kWaveWork48 = (1 << 17) - 1;
 constexpr int64_t kTwoWaves = 256;
 
-static int site_threads(const Lat &L, bool sums)
+static int site_threads(const Lat &L, bool sums, int prec = P_F64, int nrhs = 1)
 {
-    return L.V <= kTwoWaves || (sums && L.V > kWaveSites) ? kBlock : 64;
+    const bool many = sums ? L.V > kWaveSites : L.V * nrhs > (prec == P_F48 ? kWaveWork48 : kWaveWork);
+    return L.V <= kTwoWaves || many ? kBlock : 64;
 }
 
 static bool mode_sums(int mode)
@@ -269,7 +274,7 @@ hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hip
         dim3 grid((unsigned)tile_count(sh.tile) * a.nrhs + extra);
         return launch_wilson_tile(prec, mode, g5, grid, a, sh.tile, pa, st, e0, e1);
     }
-    const int nt = mode_sums(mode) ? sh.nt : site_threads(L, false);
+    const int nt = mode_sums(mode) ? sh.nt : site_threads(L, false, prec, a.nrhs);
     dim3 grid(blocks_of(L, nt) * a.nrhs + extra);
     if (prec == P_F64) wilson_dispatch<P_F64>(mode, g5, grid, nt, a, pa, st, e0, e1);
     else if (prec == P_F48) wilson_dispatch<P_F48>(mode, g5, grid, nt, a, pa, st, e0, e1);
