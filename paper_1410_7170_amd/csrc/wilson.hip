@@ -220,18 +220,32 @@ static void wilson_dispatch(int mode, bool g5, dim3 grid, int nt, const WArgs &a
     }
 }
 
-// RHS tiles in a group of the streaming form: at most three, the groups
-// alike.  An XCD holds 64 to 128 of its blocks at a time; with every RHS of a
-// block of sites side by side these span few x1 planes, and the x1 neighbours
-// miss L2, with one RHS after the other the links do.  D_W, 12 RHS, us with
-// groups of 12 / 1 / 2 / 3 / 4 / 6 / 8 (FP32, 48-bit, FP64):
-//   32^4       1004 / 932 / 919 / 914 / 919 / 916 / 938
-//              1731 / 1665 / 1581 / 1553 / 1593 / 1584 / 1671
-//              2416 / 2161 / 2093 / 2103 / 2126 / 2128 / 2278
-//   24^3x48     590 / 639 / 603 / 590 / 585 / 588 / 586 (FP32)
-// and 4 RHS at 32^3x64 with groups of 4 / 2: 636 / 623, 1099 / 1062, 1451 / 1396.
-static int group_tiles(int ntile)
+// RHS tiles in a group of the streaming form: all, or at most three where that
+// pays, the groups alike.  A die holds 32 (48-bit: 64) of its blocks at a time;
+// with every RHS of a block of sites side by side these span 8192 / nrhs sites, and
+// where that is less than an x1 plane the x1 neighbours miss L2; with one RHS after
+// the other the links do.  Lattices from 2^20 sites on gain on fewer RHS too, FP32
+// apart; below, FP64 alone gains (7 RHS in ragged groups at 16^2x64x32 0.97 on 48
+// bits).  Rates of groups of three over all side by side, D_W (FP32, 48-bit, FP64):
+//                       plane  4 RHS           6 RHS           12 RHS
+//   8x32^3     2^18     1024                                   0.96 0.95 1.00
+//   32x64x16x32 2^20     512   0.99 0.97 0.98  0.99 0.99 1.00  0.99 1.03 1.03
+//   48x24^3    0.7 M     576   0.98 1.00 1.00  1.01 1.00 1.01  1.01 0.99 1.02
+//   20x32^2x24 0.5 M     768   0.97 0.97 0.96  0.98 0.97 0.99  1.00 0.99 1.01
+//   36x24^2x32 0.7 M     768   0.98 0.98 0.99  0.99 0.98 1.01  1.01 1.01 1.07
+//   16x32^3    2^19     1024   1.00 0.99 1.02  1.00 1.00 1.03  0.99 1.00 1.06
+//   32^4       2^20     1024   0.99 1.01 1.03  1.00 1.04 1.05  1.07 1.11 1.15
+//   48x32^3    1.6 M    1024   0.98 1.00 1.04  1.01 1.05 1.11  1.11 1.22 1.27
+//   40^2x24x32 1.2 M     768   0.98 1.00 1.00  1.00 1.02 1.04  1.04 1.11 1.20
+//   16x48x32x48 1.2 M   1536   1.01 1.04 1.09  1.02 1.05 1.11  1.12 1.13 1.19
+//   16^2x64x32 2^19     2048   1.02 1.02 1.03  1.01 1.01 1.09  1.00 1.07 1.10
+// (Three: 12 RHS at 32^4 in groups of 12 / 1 / 2 / 3 / 4 / 6, FP64 us 2416 / 2161 / 2093
+// / 2103 / 2126 / 2128.)
+static int group_tiles(const Lat &L, int prec, int nrhs, int ntile)
 {
+    const int64_t plane = (int64_t)L.g.L[2] * L.g.L[3];
+    const bool wide = nrhs * plane > 8192 || (prec != P_F32 && L.V >= 1 << 20 && plane >= 768);
+    if (L.V < (prec == P_F64 ? 1 << 19 : 1 << 20) || !wide) return ntile;
     const int groups = (ntile + 2) / 3;
     return (ntile + groups - 1) / groups;
 }
@@ -261,7 +275,7 @@ hipError_t launch_wilson(const Lat &L, int prec, int mode, bool g5, WArgs a, hip
         // faster
         if (sh.blocks_per_tile > a.nblk || pa.kind) return hipErrorInvalidConfiguration;
         a.kr = sh.kr;
-        a.grp = group_tiles(sh.ntile);
+        a.grp = group_tiles(L, prec, a.nrhs, sh.ntile);
         if (prec == P_F48) a.g.Ts64 = sh.ts;   // the kernel reads its length from there
         dim3 grid((unsigned)sh.blocks_per_tile * sh.ntile);
         if (prec == P_F64) wilson_ts_dispatch<P_F64>(mode, g5, grid, sh.nt, a, st, e0, e1);
