@@ -83,8 +83,8 @@ def parse():
 # sources that define each kernel class's kernels and launches
 # (the stencils themselves, and the solvers that choose which of their modes an
 # apply launches)
-CLASS_SOURCES = {"wilson_stencil_q2": ("device.h", "scalars.h", "wilson.h", "wilson.hip", "wilson_tile.h",
-                                       "wilson_tile.hip", "blocked.hip", "mixed.hip")}
+CLASS_SOURCES = {"wilson_stencil_q2": ("device.h", "scalars.h", "tile_plan.h", "wilson.h", "wilson.hip",
+                                       "wilson_tile.h", "wilson_tile.hip", "blocked.hip", "mixed.hip")}
 
 
 def source_hash(kernel: str = "") -> str:
