@@ -223,10 +223,12 @@ static void wilson_dispatch(int mode, bool g5, dim3 grid, int nt, const WArgs &a
 // RHS tiles in a group of the streaming form: all, or at most three where that
 // pays, the groups alike.  A die holds 32 (48-bit: 64) of its blocks at a time;
 // with every RHS of a block of sites side by side these span 8192 / nrhs sites, and
-// where that is less than an x1 plane the x1 neighbours miss L2; with one RHS after
-// the other the links do.  Lattices from 2^20 sites on gain on fewer RHS too, FP32
-// apart; below, FP64 alone gains (7 RHS in ragged groups at 16^2x64x32 0.97 on 48
-// bits).  Rates of groups of three over all side by side, D_W (FP32, 48-bit, FP64):
+// where that is little more than an x1 plane the x1 neighbours miss L2; with one
+// RHS after the other the links do (D_W, 12 FP32 RHS at 24^3x48: 2.92 GB fetched
+// side by side, 2.41 in groups).  From 2^20 sites on fewer RHS gain too, FP32
+// apart; FP32 and 48-bit fields lose where the last group is not full (7 RHS: 0.97
+// at 32^4 and 16^2x64x32).  Rates of groups of three over all side by side, D_W
+// (FP32, 48-bit, FP64):
 //                       plane  4 RHS           6 RHS           12 RHS
 //   8x32^3     2^18     1024                                   0.96 0.95 1.00
 //   32x64x16x32 2^20     512   0.99 0.97 0.98  0.99 0.99 1.00  0.99 1.03 1.03
@@ -244,8 +246,9 @@ static void wilson_dispatch(int mode, bool g5, dim3 grid, int nt, const WArgs &a
 static int group_tiles(const Lat &L, int prec, int nrhs, int ntile)
 {
     const int64_t plane = (int64_t)L.g.L[2] * L.g.L[3];
-    const bool wide = nrhs * plane > 8192 || (prec != P_F32 && L.V >= 1 << 20 && plane >= 768);
-    if (L.V < (prec == P_F64 ? 1 << 19 : 1 << 20) || !wide) return ntile;
+    const bool large = prec != P_F32 && L.V >= 1 << 20 && plane >= 768;
+    const bool wide = L.V >= 1 << 19 && nrhs * plane > 6144 && (prec == P_F64 || ntile % 3 == 0);
+    if (!large && !wide) return ntile;
     const int groups = (ntile + 2) / 3;
     return (ntile + groups - 1) / groups;
 }

@@ -1,9 +1,9 @@
 """GPU check of the streaming stencil's RHS groups where a launch forms them (from
-2^19 sites on in FP64, 2^20 in FP32, a die's blocks spanning less than an x1
-plane): every RHS of groups of three and two, of two and two and of three, three
-and one, against the oracle with the stencil's tolerance of each type
-(tests/test_gpu_stencil.py); and the weighted sum of a multishift solve, whose
-partial sums come from grouped launches, by its RHS alone."""
+2^19 sites on, a die's blocks spanning little more than an x1 plane): every RHS of
+groups of three, of two and two and of three, three and one, against the oracle
+with the stencil's tolerance of each type (tests/test_gpu_stencil.py); and the
+weighted sum of a multishift solve, whose partial sums come from grouped launches,
+by its RHS alone."""
 import numpy as np
 import pytest
 import torch
@@ -18,12 +18,12 @@ M0 = -1.6
 DIMS, DIMS32 = (16, 16, 64, 32), (32, 16, 64, 32)
 
 
-@pytest.mark.parametrize("dims,prec,tol,nrhs", [(DIMS, 0, 1e-12, 7), (DIMS32, 1, 1e-6, 5), (DIMS32, 0, 1e-12, 4)])
+@pytest.mark.parametrize("dims,prec,tol,nrhs", [(DIMS, 0, 1e-12, 7), (DIMS32, 1, 1e-6, 6), (DIMS32, 0, 1e-12, 4)])
 def test_groups_match_oracle(dims, prec, tol, nrhs):
     import paper_1410_7170_amd as ovl
     print(f"rhs groups large dims={dims} nrhs={nrhs} prec={prec}", flush=True)
     lat, olat = ovl.Lattice(dims), oracle.Lattice(dims)
-    assert lat.stream_t > 0 and lat.stream_t64 > 0 and lat.V >= (1 << 20 if prec else 1 << 19)
+    assert lat.stream_t > 0 and lat.stream_t64 > 0 and lat.V >= 1 << 19
     U = synth.gauge(dims, 0.5, 171)
     G = ovl.Gauge(lat, torch.from_numpy(U).cuda(), (prec,))
     psi = synth.gaussian_spinor(lat.V, 172, nrhs)
