@@ -110,22 +110,22 @@ static StencilShape stencil_shape_ts(const Lat &L, int ts, int nrhs)
 // with 4 RHS FP64 26.8 us with four waves a block, 22.5 with one, FP32 13.0 and
 // 10.0; at 140000 sites 1.24 times as fast in FP32, 1.13 in FP64; from 280000 on
 // 0.97 to 1.01; on 48-bit fields 1.03 to 1.08 at 105000 sites, 0.91 to 1.10 from
-// 131072 on).  With partial sums up to kWaveSites
-// sites, whose sums are then at most one slot to each of the 256 strided sums;
-// beyond, every wave of a carried stage adds up more (four waves a block / one,
-// FP64 and mixed overlap apply, ms:
+// 131072 on).  With partial sums up to kWaveSites sites, whose sums are then at
+// most one slot to each of the 256 strided sums; beyond, every wave of a carried
+// stage adds up more (four waves a block / one, FP64 and mixed overlap apply, ms:
 // 8x12^3 3.77 / 3.42, 3.55 / 3.57; 10x12^3 4.06 / 3.90, 3.79 / 3.94;
 // 12^4 4.15 / 4.12, 3.95 / 4.23; 20x12^3 5.25 / 6.05, 4.70 / 5.80).  The two waves
 // per parity of 4^4 gain nothing apart, those of anything larger do (Q^2 in us:
-// 4^4 12.95 / 13.1, 6x4^3 13.8 / 12.8, 8x4^3 15.3 / 13.7, 6^4 17.2 / 14.3).
+// 4^4 12.95 / 13.1, 6x4^3 13.8 / 12.8, 8x4^3 15.3 / 13.7, 6^4 17.2 / 14.3); FP16
+// fields gain from 2000 sites on (6^4 12.8 / 13.3, 10x6^3 1.05 times as fast).
 constexpr int64_t kWaveSites = 64 * 256;
 constexpr int64_t kWaveWork = 1 << 18, kWaveWork48 = (1 << 17) - 1;
-constexpr int64_t kTwoWaves = 256;
+constexpr int64_t kTwoWaves = 256, kFew16 = 2047;
 
 static int site_threads(const Lat &L, bool sums, int prec = P_F64, int nrhs = 1)
 {
     const bool many = sums ? L.V > kWaveSites : L.V * nrhs > (prec == P_F48 ? kWaveWork48 : kWaveWork);
-    return L.V <= kTwoWaves || many ? kBlock : 64;
+    return L.V <= (prec == P_F16S ? kFew16 : kTwoWaves) || many ? kBlock : 64;
 }
 
 static bool mode_sums(int mode)
